@@ -72,6 +72,7 @@ struct spt_tensor_s {
     uint16_t* doff[8] = {};
     int32_t nsplit[8] = {}, nslots[8] = {}, nempty[8] = {};
     int64_t max_load[8] = {};
+    float repeats[8] = {};
     std::vector<int32_t> order0;  // input nonzero at each mode-0 position
     double norm_sq = 0.0;
     double prep_seconds = 0.0;
@@ -242,7 +243,7 @@ spt_status join_side(spt_tensor_s* t, hipStream_t s) {
 // partial sums go to that buffer and no timing events are recorded.
 spt_status launch_mode(spt_tensor_s* t, int mode, const uint32_t* rec_in, uint32_t* rec_out,
                        const void* const* factors, int fdtype, int rank, float* out, hipStream_t s,
-                       bool side_remap = false, float* noalloc_carry = nullptr) {
+                       bool als = false, float* noalloc_carry = nullptr) {
     if (!spt::pick_ec_exists(t->N, rank, fdtype, t->lay.words, t->lay.kind))
         return fail(SPT_ERR_UNSUPPORTED, "no kernel compiled for this mode count / rank / record size");
     const bool noalloc = noalloc_carry != nullptr;
@@ -265,6 +266,9 @@ spt_status launch_mode(spt_tensor_s* t, int mode, const uint32_t* rec_in, uint32
     a.psplit_slot = t->psplit_slot[mode];
     a.out = out;
     a.carry = carry;
+    a.nnz = t->nnz;
+    a.repeats = t->repeats[mode];
+    a.one_wave = als ? 1 : 0;
     for (int k = 0; k < N; ++k) {
         const int w = (mode + k) % N;
         a.fac[k] = factors[w];
@@ -278,7 +282,7 @@ spt_status launch_mode(spt_tensor_s* t, int mode, const uint32_t* rec_in, uint32
         return fail(SPT_ERR_HIP, "launch of the elementwise kernel failed");
     HIPCHK(hipGetLastError());
     tm.ev[1] = mark_if(s);
-    if (staged && side_remap) {
+    if (staged && als) {
         spt_status st2 = ensure_side(t);
         if (st2 != SPT_OK) return st2;
         HIPCHK(hipEventRecord(t->ev_fork, s));
@@ -313,11 +317,11 @@ spt_status launch_mode(spt_tensor_s* t, int mode, const uint32_t* rec_in, uint32
 
 // mode d's stream and, when remapping, the target buffer of the tensor
 spt_status run_mttkrp(spt_tensor_s* t, int mode, const void* const* factors, int fdtype, int rank,
-                      float* out, bool fuse, hipStream_t s, bool side_remap = false) {
+                      float* out, bool fuse, hipStream_t s, bool als = false) {
     if (t->copies)
-        return launch_mode(t, mode, t->rec_mode[mode], nullptr, factors, fdtype, rank, out, s);
+        return launch_mode(t, mode, t->rec_mode[mode], nullptr, factors, fdtype, rank, out, s, als);
     spt_status st = launch_mode(t, mode, t->rec[t->cur], fuse ? t->rec[1 - t->cur] : nullptr,
-                                factors, fdtype, rank, out, s, side_remap);
+                                factors, fdtype, rank, out, s, als);
     if (st != SPT_OK) return st;
     if (fuse) {
         t->cur = 1 - t->cur;
@@ -507,6 +511,7 @@ spt_status load_device(int32_t nmodes, const int64_t* dims, int64_t nnz, const i
             t->nslots[d] = (int32_t)mp.slot_part.size();
             t->nempty[d] = (int32_t)mp.empty_rows.size();
             t->max_load[d] = mp.max_load;
+            t->repeats[d] = (float)mp.repeats;
             if ((st = upload(t, &t->ptr[d], mp.ptr, s)) != SPT_OK) break;
             if ((st = upload(t, &t->psplit_ptr[d], mp.psplit_ptr, s)) != SPT_OK) break;
             if ((st = upload(t, &t->psplit_row[d], mp.psplit_row, s)) != SPT_OK) break;
@@ -611,6 +616,7 @@ spt_status spt_tensor_load_coo(int32_t nmodes, const int64_t* dims, int64_t nnz,
             t->nslots[d] = (int32_t)mp.slot_part.size();
             t->nempty[d] = (int32_t)mp.empty_rows.size();
             t->max_load[d] = mp.max_load;
+            t->repeats[d] = (float)mp.repeats;
             if ((st = upload(t, &t->ptr[d], mp.ptr, s)) != SPT_OK) break;
             if ((st = upload(t, &t->psplit_ptr[d], mp.psplit_ptr, s)) != SPT_OK) break;
             if ((st = upload(t, &t->psplit_row[d], mp.psplit_row, s)) != SPT_OK) break;

@@ -240,6 +240,22 @@ __global__ void nxt_kernel(const int32_t* __restrict__ bd, const int32_t* __rest
         nxt[bd[e]] = bn[e];
 }
 
+// Per window of kRunWindow stream positions (one wave each): how many carry on
+// the (output row, mode d-1 index) of the position before, and how many could.
+__global__ __launch_bounds__(kRunWindow) void run_windows_kernel(const int32_t* __restrict__ order,
+                                                                  const int32_t* __restrict__ rows,
+                                                                  const int32_t* __restrict__ last, int64_t n,
+                                                                  int32_t* __restrict__ same) {
+    const int64_t p = run_window_start((int)blockIdx.x, n) + threadIdx.x;
+    bool hit = false;
+    if (threadIdx.x > 0 && p < n) {
+        const int32_t e = order[p], f = order[p - 1];
+        hit = rows[e] == rows[f] && last[e] == last[f];
+    }
+    const uint64_t m = __ballot(hit);
+    if (threadIdx.x == 0) same[blockIdx.x] = (int32_t)__popcll(m);
+}
+
 struct PackArgs {
     const int32_t* idx;  // [N][nnz]
     const float* val;
@@ -562,9 +578,15 @@ DevicePlanError build_plan_device(int N, const int64_t* dims, int64_t nnz, const
             launch(gather_key_kernel, g, kT, s, sb.k[0], (const int32_t*)seg[w], (const int32_t*)sb.v[0], nnz);
             radix_sort(sb, nnz, bit_len(pieces[w].nseg - 1), s);
         };
+        static_assert(kRunWindow == 64, "one wave per window");
+        int32_t* same = tmp.alloc<int32_t>((int64_t)N * kRunWindows);
         for (int k = 1; k <= N; ++k) sort_by(k % N);
         for (int d = 0; d < N; ++d) {
             if (d > 0) sort_by(d);
+            if (nnz > 0)
+                launch(run_windows_kernel, kRunWindows, kRunWindow, s, (const int32_t*)sb.v[0],
+                       (const int32_t*)(didx + d * nnz), (const int32_t*)(didx + (d + N - 1) % N * nnz), nnz,
+                       same + d * kRunWindows);
             if (nnz > 0) launch(scatter_pos_kernel, g, kT, s, (const int32_t*)sb.v[0], nnz, remap[d]);
             if (d == 0) {
                 out->order0.resize(nnz);
@@ -624,7 +646,20 @@ DevicePlanError build_plan_device(int N, const int64_t* dims, int64_t nnz, const
             }
             out->norm_sq = total + carry * carry;
         }
+        std::vector<int32_t> hsame((size_t)N * kRunWindows, 0);
+        if (nnz > 0)
+            check(hipMemcpyAsync(hsame.data(), same, sizeof(int32_t) * hsame.size(), hipMemcpyDeviceToHost, s),
+                  "download");
         check(hipStreamSynchronize(s), "device planner");
+        int64_t seen = 0;
+        for (int w = 0; w < kRunWindows; ++w)
+            seen += std::max<int64_t>(0, std::min<int64_t>(nnz, run_window_start(w, nnz) + kRunWindow) -
+                                             run_window_start(w, nnz) - 1);
+        for (int d = 0; d < N; ++d) {
+            int64_t hits = 0;
+            for (int w = 0; w < kRunWindows; ++w) hits += hsame[(size_t)d * kRunWindows + w];
+            out->mode[d].repeats = seen ? (double)hits / (double)seen : 0.0;
+        }
         return DevicePlanError::kNone;
     } catch (const Fail& f) {
         *msg = f.msg;

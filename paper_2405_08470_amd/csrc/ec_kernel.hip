@@ -108,35 +108,75 @@ EcFnPtr pick_ec(int nmodes, int rank, int fdtype, int words, int kind, bool reus
     }
 }
 
-// Workgroups of f one CU holds at once (0 if the query fails).
-int resident_blocks(EcFnPtr f) {
+// Single-wave workgroups of f one CU holds at once (0 if the query fails).
+int resident_blocks(EcFnPtr f, size_t lds) {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(f), 64, 0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(f), 64, lds) != hipSuccess)
         return 0;
     return nb;
 }
 
-// The elementwise kernel of a combination: the form that reuses the last
-// gathered row when it keeps the occupancy of the plain form, else the plain
-// form (decided once per combination and device).
-EcFnPtr choose_ec(int nmodes, int rank, int fdtype, int words, int kind) {
-#ifdef SPT_EC_FORM  // build option: 0 = always the plain form, 1 = always the reuse form
-    return pick_ec(nmodes, rank, fdtype, words, kind, SPT_EC_FORM != 0);
-#endif
-    const EcFnPtr plain = pick_ec(nmodes, rank, fdtype, words, kind, false);
-    const EcFnPtr reuse = pick_ec(nmodes, rank, fdtype, words, kind, true);
-    if (!plain || !reuse) return plain;
+// Whether the form that reuses the last gathered row keeps the occupancy that
+// the gathers need: that of the plain form, or 4 waves per SIMD (decided once
+// per combination and device).
+bool reuse_fits(EcFnPtr plain, EcFnPtr reuse, size_t lds) {
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return plain;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
     static std::mutex mu;
-    static std::map<std::pair<int, EcFnPtr>, EcFnPtr> chosen;
+    static std::map<std::pair<int, EcFnPtr>, bool> fits;
     std::lock_guard<std::mutex> lock(mu);
-    auto it = chosen.find({dev, plain});
-    if (it != chosen.end()) return it->second;
-    const int occ_plain = resident_blocks(plain), occ_reuse = resident_blocks(reuse);
-    const EcFnPtr f = occ_reuse > 0 && occ_reuse >= occ_plain ? reuse : plain;
-    chosen[{dev, plain}] = f;
-    return f;
+    auto it = fits.find({dev, plain});
+    if (it != fits.end()) return it->second;
+    const int occ_plain = resident_blocks(plain, lds), occ_reuse = resident_blocks(reuse, lds);
+    return fits[{dev, plain}] = occ_reuse > 0 && occ_reuse >= std::min(occ_plain, 16);
+}
+
+// The form of the elementwise kernel and its waves per partition.
+struct EcChoice {
+    EcFnPtr f;
+    int waves;
+};
+
+// Where the lines lie (MI355X, us per launch, plain / reuse form unless said):
+// - The reuse form saves a share `repeats` of one of the N-1 gathers and pays
+//   with a branch per nonzero.  With N >= 4 that pays at every share measured:
+//   4-mode 1e7, R 16, repeats 0.15-0.71: 136-152 / 122-145; 4-mode 1e8, R 64:
+//   2692-2861 / 2282-2487; 5-mode 5e7, R 32: 860-901 / 721-802.  With N = 3 it
+//   pays on large skewed tensors (8e7, R 32: 982-1007 / 905-955; 2e7, repeats
+//   0.23-0.66: 240-246 / 226-233), not where most rows differ (8e7, repeats
+//   0.04-0.20: 1532-2053 / 1564-2106) and not on small tensors, whose rows
+//   hit the caches anyway (5e6, repeats 0.51-0.57: 57-61 / 60-66).
+// - Waves per partition: up to 256 partitions leave CUs idle or with one
+//   workgroup, so the most waves (1e5 nonzeros, 49 partitions, R 16: 39 us at 1,
+//   17 at 4, 14 at 8; 3e5, 147 partitions, R 64: 80 / 32 / 21).  Above that 4:
+//   the waves of a workgroup work on neighbouring records and share the rows
+//   they gather in L1, and 8 pay more for the combine than they gain (4-mode
+//   2e6, R 64: 127 / 72 / 76; 4-mode 1e8, R 64: 2400-2850 / 2280-2490; 1e6, R 8:
+//   35 / 23 / 31).  Without rows to share (the plain form) and with enough
+//   partitions to fill the chip twice, 1 (8e7, zipf 0.8: 1981-2053 at 1,
+//   2042-2120 at 4).
+// - CP-ALS feeds its results back, so a change of rounding grows from sweep to
+//   sweep: its sums stay those of one wave per partition, bit for bit.  There
+//   the reuse form pays only where the partitions fill the chip (4-mode 1e8:
+//   2752-3090 / 2396-2853; 1e6, R 8, 611 partitions: 31-43 / 34-47).
+
+EcChoice choose_ec(int nmodes, int rank, int fdtype, int words, int kind, int kappa, const EcArgs& a) {
+    EcChoice c{pick_ec(nmodes, rank, fdtype, words, kind, false), 1};
+    const EcFnPtr reuse = pick_ec(nmodes, rank, fdtype, words, kind, true);
+    if (!c.f || !reuse) return {nullptr, 1};
+#ifdef SPT_EC_FORM  // build option: 0 = always the plain form, 1 = always the reuse form
+    const bool want = SPT_EC_FORM != 0;
+#else
+    const bool pays = (nmodes >= 4 && !(a.one_wave && kappa < 4096)) || (a.repeats >= 0.4f && kappa >= 4096);
+    const bool want = pays && reuse_fits(c.f, reuse, ec_lds_bytes(nmodes, rank, fdtype, 1));
+#endif
+    if (want) c.f = reuse;
+#ifdef SPT_EC_WAVES  // build option: waves per partition
+    c.waves = SPT_EC_WAVES;
+#else
+    c.waves = a.one_wave ? 1 : kappa <= 256 ? 8 : (!want && kappa >= 8192) ? 1 : 4;
+#endif
+    return c;
 }
 
 }  // namespace
@@ -148,9 +188,12 @@ bool pick_ec_exists(int nmodes, int rank, int fdtype, int words, int kind) {
 bool launch_ec(int nmodes, int rank, int fdtype, int words, int kind, int kappa, const EcArgs& a,
                hipStream_t s) {
     if (kappa <= 0) return pick_ec(nmodes, rank, fdtype, words, kind, false) != nullptr;
-    const EcFnPtr f = choose_ec(nmodes, rank, fdtype, words, kind);
-    if (!f) return false;
-    hipLaunchKernelGGL(f, dim3((unsigned)kappa), dim3(64), 0, s, a);
+    const EcChoice c = choose_ec(nmodes, rank, fdtype, words, kind, kappa, a);
+    if (!c.f) return false;
+    EcArgs args = a;
+    args.waves = c.waves;
+    hipLaunchKernelGGL(c.f, dim3((unsigned)kappa), dim3((unsigned)(64 * args.waves)),
+                       (size_t)ec_lds_bytes(nmodes, rank, fdtype, args.waves), s, args);
     return true;
 }
 

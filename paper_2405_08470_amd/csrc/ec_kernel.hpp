@@ -1,22 +1,25 @@
 // Fused elementwise computation (Alg. 2) and dynamic remapping (Alg. 3) for
 // one output mode, mapped to gfx950 wavefronts (the role of Alg. 4).
 //
-// One workgroup = one wave64 = one partition B_{d,z} of Alg. 1.  A nonzero
-// is handled by L = R/4 lanes, each holding 4 consecutive ranks (one 16-byte
-// load per gathered factor row per lane, so a row of R FP32 values arrives
-// in one request).  The wave splits its partition into G = 64/L contiguous
-// sub-ranges, one per lane group; a group walks its sub-range in stream
-// order, so runs of equal output row (the stream is grouped by row) are
-// summed in registers and each finished row is stored once.  A row that
-// crosses a sub-range boundary is finished by a short chain combine in LDS
-// at the end.  Rows split across partitions (pieces, see the planner) go to
-// a carry slot instead, summed later by the fixup kernel.  No atomics.
+// One workgroup = one partition B_{d,z} of Alg. 1, in S waves of 64 lanes (S
+// chosen by the launch: 1 where the partitions alone fill the chip).  A
+// nonzero is handled by L = R/4 lanes, each holding 4 consecutive ranks (one
+// 16-byte load per gathered factor row per lane, so a row of R FP32 values
+// arrives in one request).  The workgroup splits its partition into S*G
+// contiguous sub-ranges, G = 64/L, one per lane group; a group walks its
+// sub-range in stream order, so runs of equal output row (the stream is
+// grouped by row) are summed in registers and each finished row is stored
+// once.  A row that crosses a sub-range boundary is finished by a short chain
+// combine in LDS at the end.  Rows split across partitions (pieces, see the
+// planner) go to a carry slot instead, summed later by the fixup kernel.  No
+// atomics.
 //
 // Records are fetched one step ahead, one per lane (software pipeline),
 // which is also where each record is written to its remap position in the
 // next mode's stream (Alg. 3).  Each lane decodes the record it fetched into
-// LDS once; the gathers of several nonzeros are issued before any of them is
-// consumed.
+// its wave's part of LDS once; the gathers of several nonzeros are issued
+// before any of them is consumed.  The waves of a workgroup meet only before
+// and after their walks.
 #pragma once
 
 #include <algorithm>
@@ -50,6 +53,18 @@ __device__ __forceinline__ uint32_t decode(const Rec<RW>& r, const EcArgs& a) {
             return (uint32_t)x & a.fmask[W];
         }
     }
+}
+
+// Orders a wave's LDS accesses before and after it (the waves of a workgroup
+// keep their own staging, so no workgroup barrier is needed).  LDS accesses of
+// one wave are carried out in order, so this only holds the compiler; the lane
+// exchange of a constant makes every lane of the wave take part and costs
+// nothing.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    (void)__builtin_amdgcn_readlane(0, 0);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 template <int RW, int KIND, int... W>
@@ -111,34 +126,62 @@ __device__ __forceinline__ void store_vals(float* dst, const float (&v)[V]) {
 // run of consecutive nonzeros that share it and their output row and kept in
 // registers; every nonzero still multiplies it into its product in the same
 // order, so both forms give the same bits.  Without REUSE every nonzero
-// fetches all its gathered rows.  REUSE costs registers; the launch takes it
-// only where it keeps the occupancy.
+// fetches all its gathered rows.  REUSE costs registers and a branch per
+// nonzero; the launch says where it is taken.
+//
+// What bounds it: with rows in reach of the caches, the 64 bytes a clock each
+// CU's L1 returns (74 GB of gathered rows per launch at 4 modes, 1e8 nonzeros,
+// R 64, in 2.28-2.49 ms: 30-32 TB/s; 2.40-2.88 ms with one wave per
+// workgroup); on the 3-mode 8e7 tensor, line fetches beyond L2 (0.90-0.95 ms,
+// before 0.98-1.0); on small tensors, the chain ptr -> record -> gather ->
+// store, which more waves per partition shorten (launch choice).
+// What a lane group left to the chain combine: a row that starts in it runs on
+// past its sub-range; a row from an earlier group ends in it; ... and ends
+// before the group's last nonzero (the head partial holds its end).
+constexpr int kStarts = 1, kEnds = 2, kHead = 4;
+
+template <int N, int R, typename FT>
+struct EcShape {
+    static constexpr int V = FT::kPerLoad;
+    static constexpr int L = R / V;      // lanes per nonzero
+    static constexpr int G = 64 / L;     // lane groups of a wave = nonzeros in flight
+    static constexpr int SW = N + 2;     // staged words per nonzero: indices in mode order, value, carry slot
+};
+
 template <int N, int R, int RW, int KIND, typename FT, bool REUSE>
-__global__ __launch_bounds__(64) void ec_kernel(const EcArgs a) {
-    constexpr int V = FT::kPerLoad;
-    constexpr int L = R / V;     // lanes per nonzero
-    constexpr int G = 64 / L;    // lane groups = nonzeros in flight
+__global__ __launch_bounds__(64 * kEcMaxWaves) void ec_kernel(const EcArgs a) {
+    using Sh = EcShape<N, R, FT>;
+    constexpr int V = Sh::V;
+    constexpr int L = Sh::L;
+    constexpr int G = Sh::G;
     constexpr int NG = N - 1;    // gathered factor rows per nonzero
     // nonzeros whose gathers are issued together: the largest divisor of L
     // with at most SPT_GATHER_INFLIGHT float4 gathers in flight per lane
     constexpr int BMAX = (SPT_GATHER_INFLIGHT / NG) > 0 ? SPT_GATHER_INFLIGHT / NG : 1;
     constexpr int B = L <= BMAX ? L : (L / 2 <= BMAX ? L / 2 : (L / 4 <= BMAX ? L / 4 : (L / 8 <= BMAX ? L / 8 : 1)));
     static_assert(R % V == 0 && L >= 1 && 64 % L == 0 && L % B == 0, "rank");
-    // staged words per nonzero: indices in mode order, value, carry slot
-    constexpr int SW = N + 2;
-    constexpr int MAXSPLIT = 64;  // split rows of a partition kept in LDS
+    constexpr int SW = Sh::SW;
+    constexpr int MAXSPLIT = kEcMaxSplit;
 
-    __shared__ uint32_t stage[SW][64];
-    __shared__ float part[2][G][R];   // [0] head, [1] tail partial of a group
-    __shared__ int32_t prow[2][G];
-    __shared__ int32_t pslot[2][G];
-    __shared__ int32_t gflag[G];      // bit 0 open-left, bit 1 open-right, bit 2 non-empty
-    __shared__ uint32_t brow[G][4];   // rows at the sub-range boundaries
-    __shared__ int32_t srow[MAXSPLIT], sslot[MAXSPLIT];
+    const int SG = a.waves * G;  // lane groups of the workgroup
+    const int lane = threadIdx.x & 63;
+    const int wv = threadIdx.x >> 6;
+
+    // LDS, in the order ec_lds_bytes counts it
+    HIP_DYNAMIC_SHARED(uint4, smem)
+    float* const part0 = reinterpret_cast<float*>(smem);  // head partials of the groups
+    float* const part1 = part0 + SG * R;                  // tail partials
+    uint32_t(*const stage)[64] = reinterpret_cast<uint32_t(*)[64]>(part1 + SG * R) + wv * SW;
+    int32_t* const prow = reinterpret_cast<int32_t*>(part1 + SG * R) + a.waves * SW * 64;  // row of the tail partial
+    int32_t* const pslot = prow + SG;        // its carry slot
+    int32_t* const gflag = pslot + SG;       // after the walk: kStarts, kEnds, kHead
+    uint32_t(*const brow)[2] = reinterpret_cast<uint32_t(*)[2]>(gflag + SG);  // rows before and after a sub-range
+    int32_t* const srow = gflag + 3 * SG + wv * 2 * MAXSPLIT;                 // the wave's copy of the split rows
+    int32_t* const sslot = srow + MAXSPLIT;
 
     const int z = blockIdx.x;
-    const int lane = threadIdx.x;
-    const int g = lane / L;
+    const int gl = lane / L;                 // group within the wave
+    const int g = wv * G + gl;
     const int li = lane % L;
     const int64_t s = a.ptr[z];
     const int64_t n = a.ptr[z + 1] - s;
@@ -146,21 +189,29 @@ __global__ __launch_bounds__(64) void ec_kernel(const EcArgs a) {
     const int sp0 = a.psplit_ptr[z], sp1 = a.psplit_ptr[z + 1];
     const int nsp = sp1 - sp0;
     const bool sp_lds = nsp <= MAXSPLIT;
-    if (sp_lds && lane < nsp) {
-        srow[lane] = a.psplit_row[sp0 + lane];
-        sslot[lane] = a.psplit_slot[sp0 + lane];
-    }
     const int mode = a.rot[0];
     constexpr auto seq = std::make_integer_sequence<int, N>{};
 
-    const int64_t q = n / G, rm = n % G;
+    const int64_t q = n / SG, rm = n % SG;
     const int64_t gs = s + g * q + (g < rm ? g : rm);
     const int gn = (int)(q + (g < rm ? 1 : 0));
     const int64_t ge = gs + gn;
 
-    // output rows around the group's sub-range: before, first, last, after
-    for (int j = li; j < 4; j += L) {
-        const int64_t p = j == 0 ? gs - 1 : j == 1 ? gs : j == 2 ? ge - 1 : ge;
+    // The first records, the rows on either side of the group's sub-range and
+    // the split rows are fetched together: one round trip before the walk.
+    const bool remap_inline = a.rec_out != nullptr;
+    Rec<RW> ra, rb;
+    int32_t na = 0, nb = 0;
+    if (li < gn) {
+        load_rec<RW>(a.rec_in, gs + li, ra);
+        if (remap_inline) na = a.nxt[gs + li];
+    }
+    if (sp_lds && lane < nsp) {
+        srow[lane] = a.psplit_row[sp0 + lane];
+        sslot[lane] = a.psplit_slot[sp0 + lane];
+    }
+    for (int j = li; j < 2; j += L) {
+        const int64_t p = j == 0 ? gs - 1 : ge;
         uint32_t row = 0xFFFFFFFFu;
         if (gn > 0 && p >= s && p < s + n) {
             Rec<RW> r;
@@ -170,15 +221,9 @@ __global__ __launch_bounds__(64) void ec_kernel(const EcArgs a) {
         }
         brow[g][j] = row;
     }
-    __syncthreads();
-    const bool open_left = gn > 0 && brow[g][0] != 0xFFFFFFFFu && brow[g][0] == brow[g][1];
-    const bool open_right = gn > 0 && brow[g][3] != 0xFFFFFFFFu && brow[g][3] == brow[g][2];
-    if (li == 0) {
-        gflag[g] = (open_left ? 1 : 0) | (open_right ? 2 : 0) | (gn > 0 ? 4 : 0);
-        prow[0][g] = -1;
-        prow[1][g] = -1;
-    }
-    __syncthreads();
+    if (li == 0) gflag[g] = 0;
+    wave_sync();
+    const uint32_t before = brow[g][0], after = brow[g][1];
 
     // acc: the output row's sum so far; ylast (REUSE): the last gathered
     // mode's row of the current run of equal (output row, last gathered row)
@@ -190,10 +235,8 @@ __global__ __launch_bounds__(64) void ec_kernel(const EcArgs a) {
     }
     int cur_row = -1, cur_slot = -1;
     uint32_t cur_lrow = 0xFFFFFFFFu;  // last gathered mode's row of the current run
-    bool first_seg = true;
+    bool first_seg = true;  // still in the sub-range's first row
     const int steps = (int)(q + (rm > 0 ? 1 : 0));
-    const bool remap = a.rec_out != nullptr;
-    const bool remap_inline = remap;
 
     // carry slot of a row of this partition (-1: not a split row)
     auto slot_of = [&](int row) {
@@ -212,12 +255,6 @@ __global__ __launch_bounds__(64) void ec_kernel(const EcArgs a) {
     // the first gathers, then run the lane groups over their L nonzeros of
     // this step.  Two record buffers alternate, so a prefetch never
     // overwrites the registers of a remap store still in flight.
-    Rec<RW> ra, rb;
-    int32_t na = 0, nb = 0;
-    if (li < gn) {
-        load_rec<RW>(a.rec_in, gs + li, ra);
-        if (remap_inline) na = a.nxt[gs + li];
-    }
     auto step = [&](int step0, Rec<RW>& cur, int32_t& ncur, Rec<RW>& nxt_rec, int32_t& nnext) {
         if (step0 + li < gn) {
             if (remap_inline) store_rec<RW>(a.rec_out, ncur, cur);
@@ -225,7 +262,7 @@ __global__ __launch_bounds__(64) void ec_kernel(const EcArgs a) {
             stage[N][lane] = rword<RW - 1, RW>(cur);
             stage[N + 1][lane] = (uint32_t)slot_of((int)stage[mode][lane]);
         }
-        __syncthreads();
+        wave_sync();
         const int cnt = gn - step0;
         #pragma unroll
         for (int kb = 0; kb < L; kb += B) {
@@ -235,7 +272,7 @@ __global__ __launch_bounds__(64) void ec_kernel(const EcArgs a) {
             uint32_t orow[B], rix[B][NG];
             #pragma unroll
             for (int b = 0; b < B; ++b) {
-                const int slot = g * L + kb + b;
+                const int slot = gl * L + kb + b;
                 orow[b] = stage[mode][slot];
                 #pragma unroll
                 for (int k = 0; k < NG; ++k) rix[b][k] = stage[a.rot[k + 1]][slot];
@@ -273,7 +310,7 @@ __global__ __launch_bounds__(64) void ec_kernel(const EcArgs a) {
             #pragma unroll
             for (int b = 0; b < B; ++b) {
                 if (kb + b < cnt) {
-                    const int slot = g * L + kb + b;
+                    const int slot = gl * L + kb + b;
                     const int row = (int)orow[b];
                     if (REUSE && fresh[b]) {
                         widen<FT>(y[b][NG - 1], ylast);
@@ -281,12 +318,13 @@ __global__ __launch_bounds__(64) void ec_kernel(const EcArgs a) {
                     }
                     if (row != cur_row) {
                         if (cur_row >= 0) {
-                            if (first_seg && open_left) {
-                                store_vals<V>(&part[0][g][li * V], acc);
-                                if (li == 0) {
-                                    prow[0][g] = cur_row;
-                                    pslot[0][g] = cur_slot;
-                                }
+                            if (first_seg && before == (uint32_t)cur_row) {
+                                store_vals<V>(part0 + g * R + li * V, acc);
+                                // (this write also keeps the two stores
+                                // apart: merged, they would be one store to
+                                // either memory, and every wait for a gather
+                                // a wait for all of them)
+                                if (li == 0) gflag[g] = kHead;
                             } else {
                                 store_vals<V>(row_dst<R>(a, cur_row, cur_slot) + li * V, acc);
                             }
@@ -335,8 +373,7 @@ __global__ __launch_bounds__(64) void ec_kernel(const EcArgs a) {
                 }
             }
         }
-        __syncthreads();
-    
+        wave_sync();
     };
     for (int t = 0; t < steps; t += 2 * L) {
         step(t, ra, na, rb, nb);
@@ -344,58 +381,54 @@ __global__ __launch_bounds__(64) void ec_kernel(const EcArgs a) {
     }
 
     // the group's last segment
+    const bool open_right = cur_row >= 0 && after == (uint32_t)cur_row;
+    const bool cont = first_seg && before == (uint32_t)cur_row;  // the whole sub-range inside one longer row
     if (cur_row >= 0) {
-        if (open_right || (first_seg && open_left)) {
-            store_vals<V>(&part[1][g][li * V], acc);
+        if (open_right || cont) {
+            store_vals<V>(part1 + g * R + li * V, acc);
             if (li == 0) {
-                prow[1][g] = cur_row;
-                pslot[1][g] = cur_slot;
+                prow[g] = cur_row;
+                pslot[g] = cur_slot;
             }
         } else {
             store_vals<V>(row_dst<R>(a, cur_row, cur_slot) + li * V, acc);
         }
     }
+    if (li == 0) {
+        const int head = gflag[g];  // kHead: a row from an earlier group ended inside this one
+        gflag[g] = head | (open_right && !cont ? kStarts : 0) | (head || !open_right ? kEnds : 0);
+    }
     __syncthreads();
 
-    // chain combine across groups, lanes over ranks, in group order
-    for (int r0 = 0; r0 < R; r0 += 64) {
-        const int rk = r0 + lane;
-        const bool active = rk < R;
-        float csum = 0.0f;
-        int crow = -1, cslot = -1;
-        for (int h = 0; h < G; ++h) {
-            const int f = gflag[h];
-            if (!(f & 4)) continue;
-            const bool ol = f & 1, orr = f & 2;
-            auto flush = [&](int row, int slot, float x) {
-                if (row < 0) return;
-                if (active) row_dst<R>(a, row, slot)[rk] = x;
-            };
-            if (ol) {
-                if (prow[0][h] >= 0) {
-                    csum += active ? part[0][h][rk] : 0.0f;
-                    flush(crow, cslot, csum);
-                    crow = -1;
-                    csum = 0.0f;
-                    if (prow[1][h] >= 0) {
-                        crow = prow[1][h];
-                        cslot = pslot[1][h];
-                        csum = active ? part[1][h][rk] : 0.0f;
-                    }
-                } else {
-                    csum += active ? part[1][h][rk] : 0.0f;
-                    if (!orr) {
-                        flush(crow, cslot, csum);
-                        crow = -1;
-                        csum = 0.0f;
-                    }
+    // Chain combine: a row that runs on past its group's sub-range is summed
+    // in group order by the threads (one per rank) of the group it starts in,
+    // whose tail partial opens the chain; a group with no head partial is
+    // covered by the row as a whole.  Every chain is walked at once, eight
+    // groups' flags and partials read ahead of their use, so a workgroup of
+    // many groups waits for its longest row only.
+    for (int i = threadIdx.x; i < SG * R; i += blockDim.x) {
+        const int h = i / R, r = i % R;
+        if (!(gflag[h] & kStarts)) continue;
+        float csum = part1[i];
+        bool open = true;
+        for (int k = h + 1; open; k += 8) {
+            int f[8];
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int c = k + j < SG ? k + j : SG - 1;
+                f[j] = gflag[c];
+                v[j] = part1[c * R + r];
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if (open) {
+                    csum += (f[j] & kHead) ? part0[(k + j) * R + r] : v[j];
+                    open = !(f[j] & kEnds);
                 }
-            } else if (prow[1][h] >= 0) {
-                crow = prow[1][h];
-                cslot = pslot[1][h];
-                csum = active ? part[1][h][rk] : 0.0f;
             }
         }
+        row_dst<R>(a, prow[h], pslot[h])[r] = csum;
     }
 }
 

@@ -26,6 +26,10 @@ struct EcArgs {
     int32_t rot[8];            // rot[k] = (d + k) mod N
     int32_t foff[8];           // bit offset of each mode's index (packed layout)
     uint32_t fmask[8];         // width mask of each mode's index (packed layout)
+    int64_t nnz;
+    float repeats;             // ModePlan::repeats of mode d
+    int32_t one_wave;          // 1: one wave per partition, whose order of summation CP-ALS keeps
+    int32_t waves;             // waves per partition (set by launch_ec)
 };
 
 // Forward pass of the gradient fit (grad_kernel.hip).
@@ -51,9 +55,23 @@ struct FixupArgs {
 
 using EcFnPtr = void (*)(EcArgs);
 
+// Waves per workgroup the elementwise kernel is compiled for.
+constexpr int kEcMaxWaves = 8;
+// Split rows of a partition the elementwise kernel keeps in LDS.
+constexpr int kEcMaxSplit = 64;
+// Dynamic LDS of an elementwise workgroup of `waves` waves: the lane groups'
+// head and tail partials, each wave's staged records (indices, value, carry
+// slot), per group its tail partial's row and slot, flags and the rows on
+// either side; each wave's copy of the partition's split rows and slots.
+constexpr int ec_lds_bytes(int nmodes, int rank, int fdtype, int waves) {
+    const int per_load = fdtype == 0 ? 4 : 8;  // factor values a lane loads at once
+    const int groups = 64 * per_load / rank;
+    return waves * (2 * groups * rank * 4 + (nmodes + 2) * 64 * 4 + groups * 5 * 4 + 2 * kEcMaxSplit * 4);
+}
+
 // fdtype 0: FP32 factors, 1: BF16 factors.  Returns false if the combination
 // (nmodes, rank, factor type, record words, layout kind) has no kernel.  One
-// single-wave workgroup per partition (kappa of them).
+// workgroup per partition (kappa of them).
 bool launch_ec(int nmodes, int rank, int fdtype, int words, int kind, int kappa, const EcArgs& a,
                hipStream_t s);
 // true if the combination has an elementwise kernel

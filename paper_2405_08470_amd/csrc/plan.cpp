@@ -435,6 +435,14 @@ void build_plan(int nmodes, const int64_t* dims, int64_t nnz, const int32_t* idx
             if (d > 0) sort_by(d);
             ModePlan& mp = plan->mode[d];
             mp.order = order;
+            const int32_t *rows = idx + (int64_t)d * nnz, *last = idx + (int64_t)((d + N - 1) % N) * nnz;
+            int64_t seen = 0, same = 0;
+            for (int w = 0; w < kRunWindows; ++w) {
+                const int64_t p0 = run_window_start(w, nnz), p1 = std::min<int64_t>(nnz, p0 + kRunWindow);
+                for (int64_t p = p0 + 1; p < p1; ++p, ++seen)
+                    same += rows[order[p]] == rows[order[p - 1]] && last[order[p]] == last[order[p - 1]];
+            }
+            mp.repeats = seen ? (double)same / (double)seen : 0.0;
             mp.remap.resize(nnz);
             parallel_for(nnz, num_threads(), [&](int64_t b, int64_t e, int) {
                 for (int64_t p = b; p < e; ++p) mp.remap[order[p]] = (int32_t)p;

@@ -46,7 +46,15 @@ struct ModePlan {
     std::vector<int32_t> psplit_slot; // [nslots]
     std::vector<int32_t> empty_rows;  // rows with no nonzero
     int64_t max_load = 0;
+    // share of the stream's nonzeros with the output row and the mode-(d-1)
+    // index of the nonzero before them (from sampled windows)
+    double repeats = 0.0;
 };
+
+// ModePlan::repeats is counted over kRunWindows windows of kRunWindow
+// consecutive stream positions, evenly spaced.
+constexpr int kRunWindows = 1024, kRunWindow = 64;
+constexpr int64_t run_window_start(int w, int64_t nnz) { return (int64_t)((double)nnz / kRunWindows * w); }
 
 struct Plan {
     int nmodes = 0;

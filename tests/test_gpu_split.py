@@ -1,0 +1,62 @@
+"""The elementwise kernel at the edges of its launch choices, on the GPU:
+partition counts on both sides of the lines between 8, 4 and 1 waves per
+partition, one row over every lane group, fewer nonzeros than groups, split
+rows, every rank, FP32 and BF16 factors, and 2- to 4-mode tensors (plain and
+reuse form), against the oracle.  Tolerance: 1e-5 of M_abs per element.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2405_08470_amd import synth
+from parity import check_elementwise, mttkrp_abs
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("no GPU", allow_module_level=True)
+S = pytest.importorskip("paper_2405_08470_amd.spmttkrp")
+
+
+def _one_row(nnz):
+    e = np.arange(nnz)
+    return (3, 70, 50), np.stack([0 * e, e % 70, e % 50]).astype(np.int32)
+
+
+def _zipf(dims, nnz):
+    return dims, synth.random_coo(dims, nnz, seed=5, dist="zipf", zipf_s=1.1)[0]
+
+
+# name, (dims, indices), rank, kappa
+SHAPES = [
+    ("one_row_r8", _one_row(5001), 8, 1),
+    ("one_row_r128", _one_row(1500), 128, 1),
+    ("one_row_split", _one_row(5001), 16, 7),
+    ("fewer_than_groups", _zipf((9, 8, 7), 40), 8, 1),
+    ("kappa256", _zipf((300, 200, 4000), 60_000), 16, 256),
+    ("kappa257", _zipf((300, 200, 4000), 60_000), 16, 257),
+    ("kappa4096", _zipf((300, 200, 4000), 60_000), 32, 4096),
+    ("kappa8191", _zipf((300, 200, 4000), 60_000), 32, 8191),
+    ("kappa8192", _zipf((300, 200, 40_000), 100_000), 32, 8192),
+    ("four_modes", _zipf((300, 200, 400, 30), 60_000), 64, 300),
+    ("two_modes", _zipf((3000, 200), 60_000), 8, 300),
+]
+
+
+@pytest.mark.parametrize("name,shape,R,kappa", SHAPES, ids=[s[0] for s in SHAPES])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_split_of_partitions(name, shape, R, kappa, dtype):
+    print("case", name, dtype, flush=True)
+    dims, idx = shape
+    val = synth.normal(3, 1, idx.shape[1]).astype(np.float32)
+    Y = synth.random_factors(dims, R, seed=18)
+    exact = [oracle.bf16_round(y) for y in Y] if dtype == "bf16" else Y
+    given = [torch.from_numpy(y).cuda().to(torch.bfloat16 if dtype == "bf16" else torch.float32) for y in Y]
+    t = S.tensor_load_coo(dims, idx, val, kappa=kappa, prep="device")
+    for d in range(len(dims)):
+        out = torch.full((dims[d], R), float("nan"), device="cuda")
+        S.mttkrp(t, d, given, out, flags=S.FUSE_REMAP_NEXT)
+        ref = oracle.mttkrp(dims, idx, val, exact, d)
+        check_elementwise(out.cpu().numpy(), ref, mttkrp_abs(dims, idx, val, exact, d), label=f"{name} mode {d}")
+    t.free()
