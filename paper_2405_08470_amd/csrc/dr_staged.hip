@@ -24,7 +24,7 @@
 //                   the destination (chunks beyond 65536 records need them)
 // Destinations are distinct (nxt_d is a permutation), so the sorted order is
 // unique and does not depend on how it is computed: sub-runs of kSub records
-// are sorted in LDS, then each chunk's sub-runs are merged by rank.
+// are sorted in LDS, then each chunk's sub-runs are merged pair by pair.
 #include <hip/hip_runtime.h>
 
 #include <climits>
@@ -47,7 +47,8 @@ constexpr int kStageThreads = 256;  // table sort
 // remap workgroups of 16 waves: a quarter of the workgroups of 4-wave ones to
 // dispatch for the same records (5-7 % faster per pass on the MI355X)
 constexpr int kRemapThreads = 1024;
-constexpr int kSub = 4096;           // entries sorted in LDS by one workgroup
+constexpr int kSubShift = 12;
+constexpr int kSub = 1 << kSubShift;  // entries sorted in LDS by one workgroup
 
 // One workgroup per run of C consecutive entries: bitonic sort of (destination,
 // offset) pairs in LDS.
@@ -89,34 +90,36 @@ __global__ __launch_bounds__(kStageThreads) void stage_tables_kernel(const int32
     }
 }
 
-// Merge of the sorted sub-runs of each chunk of 2^cshift entries: an entry's
-// place in its chunk is its place in its own sub-run plus the number of
-// smaller destinations in the chunk's other sub-runs (binary searches;
-// destinations are distinct).  Offsets become offsets inside the chunk.
-__global__ __launch_bounds__(kStageThreads) void merge_runs_kernel(const int32_t* __restrict__ sdst,
-                                                                   const uint16_t* __restrict__ soff,
-                                                                   int64_t nnz, int cshift, int dbits,
-                                                                   int32_t* __restrict__ ddst,
-                                                                   uint16_t* __restrict__ doff) {
+// One level of the merge of a chunk's sorted runs: runs of 2^rshift entries
+// pair up (2^rshift < chunk); an entry's place in the pair is its place in its
+// own run plus the number of smaller destinations in the other (one binary
+// search; destinations are distinct).  Offsets become offsets inside the
+// pair.  LAST (the pair is the chunk): the offset's bits above 16 go into the
+// destination word.  What bounds it is the searches' reads, rshift + 1 per
+// entry and level: five levels from 4096 to 131072 take 70 per entry where one
+// search in each of the chunk's 31 other runs took 372 (1e7 records: 0.61 against
+// 1.78 ms on the MI355X).
+template <bool LAST>
+__global__ __launch_bounds__(kStageThreads) void merge_pairs_kernel(const int32_t* __restrict__ sdst,
+                                                                    const uint16_t* __restrict__ soff, int64_t nnz,
+                                                                    int rshift, int dbits, int32_t* __restrict__ ddst,
+                                                                    uint16_t* __restrict__ doff) {
     const int64_t i = blockIdx.x * (int64_t)kStageThreads + threadIdx.x;
     if (i >= nnz) return;
-    const int64_t c0 = (i >> cshift) << cshift;
-    const int64_t r0 = (i / kSub) * kSub;
-    const int64_t cend = (c0 + (int64_t(1) << cshift)) < nnz ? c0 + (int64_t(1) << cshift) : nnz;
+    const int64_t run = int64_t(1) << rshift;
+    const int64_t r0 = i & ~(run - 1), p0 = i & ~(2 * run - 1);
+    const int64_t o0 = r0 ^ run;  // the other run of the pair
     const int32_t key = sdst[i];
-    int64_t pos = i - r0;
-    for (int64_t rs = c0; rs < cend; rs += kSub) {
-        if (rs == r0) continue;
-        int64_t lo = rs, hi = (rs + kSub) < cend ? rs + kSub : cend;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            if (sdst[mid] < key) lo = mid + 1; else hi = mid;
-        }
-        pos += lo - rs;
+    int64_t lo = o0 < nnz ? o0 : nnz, hi = o0 + run < nnz ? o0 + run : nnz;
+    const int64_t first = lo;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (sdst[mid] < key) lo = mid + 1; else hi = mid;
     }
-    const uint32_t off = (uint32_t)((r0 - c0) + soff[i]);
-    ddst[c0 + pos] = (int32_t)((uint32_t)key | ((off >> 16) << dbits));
-    doff[c0 + pos] = (uint16_t)(off & 0xFFFFu);
+    const int64_t pos = p0 + (i - r0) + (lo - first);
+    const uint32_t off = (uint32_t)(r0 - p0) + soff[i];
+    ddst[pos] = LAST ? (int32_t)((uint32_t)key | ((off >> 16) << dbits)) : key;
+    doff[pos] = (uint16_t)(off & 0xFFFFu);
 }
 
 // One record per thread: slot j of the tables, read from its chunk in L2.
@@ -127,10 +130,14 @@ __global__ __launch_bounds__(kRemapThreads) void remap_flat_kernel(const uint32_
                                                                     const uint16_t* __restrict__ doff,
                                                                     int64_t nnz, int cshift, int dbits) {
     // the grid is a multiple of 8 chunks; block b runs on XCD b % 8 and takes
-    // the (b / 8)-th block of that XCD's chunks c = x, x + 8, x + 16, ...
+    // the (b / 8)-th block of that XCD's chunks c = x, x + 8, x + 16, ...  Up
+    // to 8 chunks (one per XCD) the grid is as long as the stream instead:
+    // all of it stays in the caches, and whole chunks of workgroups without
+    // records cost more than they order (1e5 records: 6.3 us with 1024
+    // workgroups; a 3-mode pass of 51 us takes 43 us with 98).
     const unsigned bpc = (1u << cshift) / kRemapThreads;  // workgroups per chunk
     const unsigned b = blockIdx.x, x = b % 8u, r = b / 8u;
-    const unsigned v = ((r / bpc) * 8u + x) * bpc + r % bpc;
+    const unsigned v = gridDim.x < 8u * bpc ? b : ((r / bpc) * 8u + x) * bpc + r % bpc;
     const int64_t j = (int64_t)v * kRemapThreads + threadIdx.x;
     if (j >= nnz) return;
     const uint32_t t = (uint32_t)ddst[j];
@@ -152,7 +159,7 @@ int dest_bits(int64_t nnz) {
 // what 16 bits of doff and the 32 - dbits spare bits of ddst address.
 int chunk_shift(int words, int64_t nnz) {
     const int maxsh = 16 + (32 - dest_bits(nnz));
-    int sh = 12;
+    int sh = kSubShift;
     while (sh < maxsh && sh < 24 && ((int64_t(1) << (sh + 1)) * words * 4 <= (int64_t)SPT_STAGE_CHUNK_BYTES)) ++sh;
     return sh;
 }
@@ -166,11 +173,26 @@ void launch_stage_tables(int words, const int32_t* nxt, int64_t nnz, int32_t* dd
     if (nnz == 0) return;
     const int cshift = chunk_shift(words, nnz);
     const unsigned subs = (unsigned)((nnz + kSub - 1) / kSub);
-    hipLaunchKernelGGL(stage_tables_kernel<kSub>, dim3(subs), dim3(kStageThreads), 0, s, nxt, nnz, tmp_dst,
-                       tmp_off);
     const unsigned blocks = (unsigned)((nnz + kStageThreads - 1) / kStageThreads);
-    hipLaunchKernelGGL(merge_runs_kernel, dim3(blocks), dim3(kStageThreads), 0, s, (const int32_t*)tmp_dst,
-                       (const uint16_t*)tmp_off, nnz, cshift, dest_bits(nnz), ddst, doff);
+    // the runs alternate between the tables and the temporaries, so that the
+    // last level writes the tables
+    int32_t *from_dst = (cshift - kSubShift) % 2 ? tmp_dst : ddst, *to_dst = (cshift - kSubShift) % 2 ? ddst : tmp_dst;
+    uint16_t *from_off = (cshift - kSubShift) % 2 ? tmp_off : doff, *to_off = (cshift - kSubShift) % 2 ? doff : tmp_off;
+    hipLaunchKernelGGL(stage_tables_kernel<kSub>, dim3(subs), dim3(kStageThreads), 0, s, nxt, nnz, from_dst, from_off);
+    for (int r = kSubShift; r < cshift; ++r) {
+        if (r + 1 == cshift)
+            hipLaunchKernelGGL((merge_pairs_kernel<true>), dim3(blocks), dim3(kStageThreads), 0, s,
+                               (const int32_t*)from_dst, (const uint16_t*)from_off, nnz, r, dest_bits(nnz), to_dst, to_off);
+        else
+            hipLaunchKernelGGL((merge_pairs_kernel<false>), dim3(blocks), dim3(kStageThreads), 0, s,
+                               (const int32_t*)from_dst, (const uint16_t*)from_off, nnz, r, dest_bits(nnz), to_dst, to_off);
+        int32_t* const d = from_dst;
+        from_dst = to_dst;
+        to_dst = d;
+        uint16_t* const o = from_off;
+        from_off = to_off;
+        to_off = o;
+    }
 }
 
 void launch_remap_staged(int words, int64_t nnz, const uint32_t* in, uint32_t* out, const int32_t* ddst,
@@ -178,7 +200,8 @@ void launch_remap_staged(int words, int64_t nnz, const uint32_t* in, uint32_t* o
     if (nnz == 0) return;
     const int cshift = chunk_shift(words, nnz), dbits = dest_bits(nnz);
     const int64_t nchunks = (nnz + (int64_t(1) << cshift) - 1) >> cshift;
-    const unsigned blocks = (unsigned)(((nchunks + 7) / 8) * 8 * ((int64_t(1) << cshift) / kRemapThreads));
+    const unsigned blocks = (unsigned)(nchunks < 8 ? (nnz + kRemapThreads - 1) / kRemapThreads
+                                                   : (nchunks + 7) / 8 * 8 * ((int64_t(1) << cshift) / kRemapThreads));
     if (words == 3)
         hipLaunchKernelGGL((remap_flat_kernel<3>), dim3(blocks), dim3(kRemapThreads), 0, s, in, out, ddst, doff,
                            nnz, cshift, dbits);
