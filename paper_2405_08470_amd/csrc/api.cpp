@@ -73,7 +73,8 @@ struct spt_tensor_s {
     int32_t nsplit[8] = {}, nslots[8] = {}, nempty[8] = {};
     int64_t max_load[8] = {};
     float repeats[8] = {};
-    std::vector<int32_t> order0;  // input nonzero at each mode-0 position
+    std::vector<int32_t> order0;  // input nonzero at each mode-0 position (host planner)
+    int32_t* order0_dev = nullptr;  // ... of the device planner, read by spt_tensor_get_remap only
     double norm_sq = 0.0;
     double prep_seconds = 0.0;
     int64_t device_bytes = 0;
@@ -540,7 +541,7 @@ spt_status load_device(int32_t nmodes, const int64_t* dims, int64_t nnz, const i
             delete t;
             return st;
         }
-        t->order0 = std::move(dp.order0);
+        t->order0_dev = dp.order0;
         t->cur = 0;
         t->cur_mode = 0;
     } catch (const std::bad_alloc&) {
@@ -1017,7 +1018,12 @@ spt_status spt_tensor_get_remap(spt_tensor_t t, int32_t mode, int64_t* b_host) {
         // b_0 from the mode-0 stream, then follow the device's next-position
         // arrays mode by mode
         std::vector<int32_t> pos(nnz), nx(nnz);
-        for (int64_t p = 0; p < nnz; ++p) pos[t->order0[p]] = (int32_t)p;
+        const int32_t* order0 = t->order0.data();
+        if (t->order0_dev) {
+            if (nnz) HIPCHK(hipMemcpy(nx.data(), t->order0_dev, sizeof(int32_t) * nnz, hipMemcpyDeviceToHost));
+            order0 = nx.data();
+        }
+        for (int64_t p = 0; p < nnz; ++p) pos[order0[p]] = (int32_t)p;
         for (int d = 0; d < mode; ++d) {
             if (nnz) HIPCHK(hipMemcpy(nx.data(), t->nxt[d], sizeof(int32_t) * nnz, hipMemcpyDeviceToHost));
             for (int64_t e = 0; e < nnz; ++e) pos[e] = nx[pos[e]];

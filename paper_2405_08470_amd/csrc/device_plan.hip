@@ -354,18 +354,40 @@ struct Fail {
     std::string msg;
 };
 
+// Device memory of one call.  It is taken in one piece where that can be had
+// (27 buffers allocated and freed one by one cost 5 of the 32 ms of a load of
+// 1e7 nonzeros), else buffer by buffer.
 struct Temps {
     std::vector<void*> ptrs;
     hipStream_t stream = nullptr;
+    char* slab = nullptr;
+    size_t left = 0;
     ~Temps() {
         // kernels of a failed call may still read these
         (void)hipStreamSynchronize(stream);
         for (void* p : ptrs) (void)hipFree(p);
     }
+    void reserve(size_t bytes) {
+        void* p = nullptr;
+        if (hipMalloc(&p, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
+        ptrs.push_back(p);
+        slab = static_cast<char*>(p);
+        left = bytes;
+    }
     template <typename T>
     T* alloc(int64_t count) {
+        const size_t bytes = ((size_t)std::max<int64_t>(1, count) * sizeof(T) + 255) / 256 * 256;
+        if (bytes <= left) {
+            char* const at = slab;
+            slab += bytes;
+            left -= bytes;
+            return reinterpret_cast<T*>(at);
+        }
         void* p = nullptr;
-        if (hipMalloc(&p, (size_t)std::max<int64_t>(1, count) * sizeof(T)) != hipSuccess)
+        if (hipMalloc(&p, bytes) != hipSuccess)
             throw Fail{DevicePlanError::kOom, "device allocation failed in the device planner"};
         ptrs.push_back(p);
         return static_cast<T*>(p);
@@ -471,6 +493,12 @@ DevicePlanError build_plan_device(int N, const int64_t* dims, int64_t nnz, const
         tmp.stream = s;
         int64_t maxI = 1;
         for (int w = 0; w < N; ++w) maxI = std::max<int64_t>(maxI, dims[w]);
+        // indices, values, sort buffers (4), per mode: row-sorted keys and
+        // nonzeros, segments, remap ids and row ends; sort histograms, scans,
+        // run sums and segment tables in the rest
+        int64_t rows = 0;
+        for (int w = 0; w < N; ++w) rows += dims[w];
+        tmp.reserve((size_t)(5 * N + 5) * 4 * nnz + (size_t)nnz / 2 + (size_t)rows * 20 + (size_t(4) << 20));
         int32_t* didx = tmp.alloc<int32_t>(N * nnz);
         float* dval = tmp.alloc<float>(nnz);
         if (nnz > 0) {
@@ -588,11 +616,10 @@ DevicePlanError build_plan_device(int N, const int64_t* dims, int64_t nnz, const
                        (const int32_t*)(didx + d * nnz), (const int32_t*)(didx + (d + N - 1) % N * nnz), nnz,
                        same + d * kRunWindows);
             if (nnz > 0) launch(scatter_pos_kernel, g, kT, s, (const int32_t*)sb.v[0], nnz, remap[d]);
-            if (d == 0) {
-                out->order0.resize(nnz);
+            if (d == 0 && !copies) {
+                out->order0 = static_cast<int32_t*>(palloc(sizeof(int32_t) * nnz));
                 if (nnz > 0)
-                    check(hipMemcpyAsync(out->order0.data(), sb.v[0], sizeof(int32_t) * nnz, hipMemcpyDeviceToHost, s),
-                          "download order");
+                    check(hipMemcpyAsync(out->order0, sb.v[0], sizeof(int32_t) * nnz, hipMemcpyDeviceToDevice, s), "copy");
             }
             if (copies || d == 0) {
                 uint32_t* r = static_cast<uint32_t*>(palloc(sizeof(uint32_t) * lay.words * nnz));
