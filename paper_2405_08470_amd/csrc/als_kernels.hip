@@ -246,10 +246,67 @@ __global__ __launch_bounds__(256) void normal_inverse_kernel(const double* __res
         for (int e = 0; e < P * P; ++e) c[e] = g[e] = v[e];
         ok = spd_inverse<R>(c, g, l);
     }
-    if (!ok && tid == 0) status[0] |= 1;
+    // a sweep starts with mode 0
+    if (tid == 0) status[0] = (mode == 0 ? 0 : status[0]) | (ok ? 0 : 1);
     if (on)
 #pragma unroll
         for (int e = 0; e < P * P; ++e) Vinv[(ti + T * (e / P)) * R + tj + T * (e % P)] = ok ? g[e] : 0.0;
+}
+
+// Sums the four waves' Gram tiles (c0 <= c1, register v of lane l: row 4 v +
+// l / 16, column l % 16 of the tile) in a fixed order, (0 + 2) + (1 + 3), and
+// writes the whole symmetric matrix to dst.  Each wave adds whole registers
+// from LDS, every load issued before the first add; the waves adding into one
+// LDS matrix in turn was a chain of read-modify-writes that took 18 of a
+// workgroup's 34 us at R = 64.
+template <int R>
+struct GramTiles {
+    static constexpr int CT = R / 16;
+    static constexpr int NP = CT * (CT + 1) / 2;
+    // doubles of LDS: two waves' tiles, then the matrix
+    static constexpr int lds = 2 * NP * 256 > R * R ? 2 * NP * 256 : R * R;
+};
+
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+template <int R>
+__device__ void store_block_gram(v4d (&gacc)[GramTiles<R>::NP], double* buf, double* __restrict__ dst) {
+    constexpr int CT = GramTiles<R>::CT, NP = GramTiles<R>::NP;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int rl = lane & 15, q = lane >> 4;
+    for (int half = 2; half >= 1; half >>= 1) {
+        if (wv >= half && wv < 2 * half) {
+            double* const mine = buf + (wv - half) * NP * 256 + lane;
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) mine[(4 * p + v) * 64] = gacc[p][v];
+        }
+        __syncthreads();
+        if (wv < half) {
+            const double* const other = buf + wv * NP * 256 + lane;
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) gacc[p][v] += other[(4 * p + v) * 64];
+        }
+        __syncthreads();
+    }
+    if (wv == 0) {
+        int p = 0;
+#pragma unroll
+        for (int c0 = 0; c0 < CT; ++c0)
+#pragma unroll
+            for (int c1 = c0; c1 < CT; ++c1, ++p)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int i = 16 * c0 + 4 * v + q, j = 16 * c1 + rl;
+                    buf[i * R + j] = gacc[p][v];
+                    if (c1 != c0) buf[j * R + i] = gacc[p][v];
+                }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < R * R; e += 256) dst[e] = buf[e];
 }
 
 template <int R>
@@ -307,14 +364,14 @@ __global__ __launch_bounds__(256) void solve_rows_kernel(const float* __restrict
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int e = tid + 256 * k;
-        if (e < E) gpart[(int64_t)blockIdx.x * E + e] = gacc[k];
+        if (e < E) gpart[(int64_t)blockIdx.x * (E + R) + e] = gacc[k];
     }
     ired[bi][col] = iacc;
     __syncthreads();
     if (tid < R) {
         double s = 0.0;
         for (int i = 0; i < RB; ++i) s += ired[i][tid];
-        ipart[(int64_t)blockIdx.x * R + tid] = s;
+        ipart[(int64_t)blockIdx.x * (E + R) + tid] = s;
     }
 }
 
@@ -338,12 +395,11 @@ __global__ __launch_bounds__(256) void solve_rows_mfma_kernel(const float* __res
                                                                double* __restrict__ gpart,
                                                                double* __restrict__ ipart) {
     static_assert(R % 16 == 0, "rank");
-    typedef double v4d __attribute__((ext_vector_type(4)));
     constexpr int CT = R / 16;             // column tiles
     constexpr int KS = R / 4;              // steps of the solve
     constexpr int NP = CT * (CT + 1) / 2;  // Gram tiles c0 <= c1
     constexpr int E = R * R;
-    __shared__ double gsh[E];
+    __shared__ double buf[GramTiles<R>::lds];
     __shared__ double ish[4][4][R];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int rl = lane & 15, q = lane >> 4;
@@ -422,35 +478,15 @@ __global__ __launch_bounds__(256) void solve_rows_mfma_kernel(const float* __res
                     gacc[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(yd[c0][v], yd[c1][v], gacc[p], 0, 0, 0);
         }
     }
-    // the waves' Gram tiles (and their transposes) summed in LDS in wave
-    // order; every entry belongs to one lane of a wave
-    for (int w = 0; w < 4; ++w) {
-        if (wv == w) {
-            int p = 0;
-#pragma unroll
-            for (int c0 = 0; c0 < CT; ++c0)
-#pragma unroll
-                for (int c1 = c0; c1 < CT; ++c1, ++p)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int i = 16 * c0 + 4 * v + q, j = 16 * c1 + rl;
-                        const double x = gacc[p][v];
-                        gsh[i * R + j] = w == 0 ? x : gsh[i * R + j] + x;
-                        if (c1 != c0) gsh[j * R + i] = w == 0 ? x : gsh[j * R + i] + x;
-                    }
-        }
-        __syncthreads();
-    }
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) ish[wv][q][16 * ct + rl] = iacc[ct];
-    __syncthreads();
-    for (int e = threadIdx.x; e < E; e += 256) gpart[(int64_t)blockIdx.x * E + e] = gsh[e];
+    store_block_gram<R>(gacc, buf, gpart + (int64_t)blockIdx.x * (E + R));
     if (threadIdx.x < R) {
         const int c = threadIdx.x;
         double t = 0.0;
         for (int w = 0; w < 4; ++w)
             for (int g = 0; g < 4; ++g) t += ish[w][g][c];
-        ipart[(int64_t)blockIdx.x * R + c] = t;
+        ipart[(int64_t)blockIdx.x * (E + R) + c] = t;
     }
 }
 
@@ -458,17 +494,14 @@ __global__ __launch_bounds__(256) void solve_rows_mfma_kernel(const float* __res
 // wave takes 16-row tiles; lane (rl = lane % 16, q = lane / 16) holds
 // Y(r0 + 4v + q, 16c + rl), which is both the A operand (column tile c0 of
 // Y^T) and the B operand (column tile c1 of Y) of v_mfma_f64_16x16x4f64 for
-// the 4 rows r0 + 4v .. r0 + 4v + 3.  The waves' tiles are summed in LDS in
-// wave order, and the block writes partial[blockIdx][R*R].
+// the 4 rows r0 + 4v .. r0 + 4v + 3.  The block writes partial[blockIdx][R*R].
 template <int R>
 __global__ __launch_bounds__(256) void gram_mfma_kernel(const float* __restrict__ Y, int64_t rows,
                                                          double* __restrict__ partial) {
     static_assert(R % 16 == 0, "rank");
-    typedef double v4d __attribute__((ext_vector_type(4)));
     constexpr int CT = R / 16;
     constexpr int NP = CT * (CT + 1) / 2;
-    constexpr int E = R * R;
-    __shared__ double gsh[E];
+    __shared__ double buf[GramTiles<R>::lds];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int rl = lane & 15, q = lane >> 4;
     v4d gacc[NP];
@@ -494,24 +527,7 @@ __global__ __launch_bounds__(256) void gram_mfma_kernel(const float* __restrict_
                     gacc[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(yd[c0][v], yd[c1][v], gacc[p], 0, 0, 0);
         }
     }
-    for (int w = 0; w < 4; ++w) {
-        if (wv == w) {
-            int p = 0;
-#pragma unroll
-            for (int c0 = 0; c0 < CT; ++c0)
-#pragma unroll
-                for (int c1 = c0; c1 < CT; ++c1, ++p)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int i = 16 * c0 + 4 * v + q, j = 16 * c1 + rl;
-                        const double x = gacc[p][v];
-                        gsh[i * R + j] = w == 0 ? x : gsh[i * R + j] + x;
-                        if (c1 != c0) gsh[j * R + i] = w == 0 ? x : gsh[j * R + i] + x;
-                    }
-        }
-        __syncthreads();
-    }
-    for (int e = threadIdx.x; e < E; e += 256) partial[(int64_t)blockIdx.x * E + e] = gsh[e];
+    store_block_gram<R>(gacc, buf, partial + (int64_t)blockIdx.x * R * R);
 }
 
 template <int R>
@@ -524,9 +540,10 @@ __global__ __launch_bounds__(256) void als_finish_kernel(const double* __restric
                                                           double* __restrict__ fit) {
     constexpr int E = R * R;
     __shared__ double lam[R];
-    __shared__ double red[256];
+    __shared__ double red[256], red16[16], isum[R];
     const int tid = threadIdx.x;
     if (tid < R) {
+        isum[tid] = Isum[tid];
         lam[tid] = sqrt(Gun[tid * R + tid]);
         lambda[tid] = lam[tid];
     }
@@ -549,11 +566,22 @@ __global__ __launch_bounds__(256) void als_finish_kernel(const double* __restric
     }
     red[tid] = xh;
     __syncthreads();
+    // 16 sums of 16, then their sum: one chain of 256 dependent LDS reads was
+    // most of this kernel's time
+    if (tid < 16) {
+        double t = 0.0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) t += red[16 * tid + i];
+        red16[tid] = t;
+    }
+    __syncthreads();
     if (tid == 0) {
         double x = 0.0;
-        for (int i = 0; i < 256; ++i) x += red[i];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x += red16[i];
         double in = 0.0;
-        for (int r = 0; r < R; ++r) in += Isum[r];
+#pragma unroll
+        for (int r = 0; r < R; ++r) in += isum[r];
         double res2 = normX2 + x - 2.0 * in;
         if (res2 < 0.0) res2 = 0.0;
         fit[0] = 1.0 - sqrt(res2) / sqrt(normX2);
@@ -581,11 +609,6 @@ __global__ void scale_cols_kernel(float* __restrict__ Y, int64_t rows,
     }
 }
 
-__global__ void zero_i32_kernel(int32_t* p, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
-}
-
 template <template <int> class K, typename... Args>
 void by_rank(int rank, dim3 grid, dim3 block, hipStream_t s, Args... args) {
     switch (rank) {
@@ -609,8 +632,11 @@ template <int R> struct Scale { static constexpr auto fn = scale_cols_kernel<R>;
 
 }  // namespace
 
+// One 16-row tile per wave up to 65536 rows: below that the kernels wait on
+// latency, not on the partials' reduction (R 64, 12007 rows: PLACEHOLDER us with 4
+// tiles per wave, PLACEHOLDER with one).
 int gram_blocks(int64_t rows) {
-    return (int)std::max<int64_t>(1, std::min<int64_t>(1024, (rows + 255) / 256));
+    return (int)std::max<int64_t>(1, std::min<int64_t>(1024, (rows + 63) / 64));
 }
 
 void launch_gram_partial(int rank, const float* Y, int64_t rows, double* partial, hipStream_t s) {
@@ -631,9 +657,7 @@ void launch_normal_inverse(int rank, int nmodes, int mode, const double* grams, 
     by_rank<NormInv>(rank, dim3(1), dim3(256), s, grams, nmodes, mode, Vinv, status);
 }
 
-int solve_blocks(int64_t rows) {
-    return (int)std::max<int64_t>(1, std::min<int64_t>(1024, (rows + 255) / 256));
-}
+int solve_blocks(int64_t rows) { return gram_blocks(rows); }
 
 void launch_solve_rows(int rank, const float* M, const double* Vinv, int64_t rows, float* Y,
                        double* gpart, double* ipart, hipStream_t s) {
@@ -656,11 +680,6 @@ void launch_scale_cols(int rank, float* Y, int64_t rows, const double* lambda, h
     if (total4 == 0) return;
     const int64_t blocks = std::min<int64_t>((total4 + 255) / 256, int64_t(1) << 20);
     by_rank<Scale>(rank, dim3((unsigned)blocks), dim3(256), s, Y, rows, lambda);
-}
-
-void launch_zero_i32(int32_t* p, int n, hipStream_t s) {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(zero_i32_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p, n);
 }
 
 }  // namespace spt

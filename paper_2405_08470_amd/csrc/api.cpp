@@ -96,7 +96,11 @@ struct spt_tensor_s {
     double* Isum = nullptr;
     double* fitd = nullptr;
     int32_t* status = nullptr;
-    int32_t* status_host = nullptr;
+    struct SweepResult {
+        double fit;
+        int32_t status;
+    };
+    SweepResult* result = nullptr;  // pinned host memory
     hipEvent_t status_event = nullptr;
     // CP-ALS: the remap pass of a mode on a side stream, beside that mode's
     // fixup and dense update (joined before the next mode's EC)
@@ -143,7 +147,7 @@ void release(spt_tensor_s* t) {
     t->event_pool.clear();
     for (void* p : t->allocs) (void)hipFree(p);
     for (void* p : t->ws_allocs) (void)hipFree(p);
-    if (t->status_host) (void)hipHostFree(t->status_host);
+    if (t->result) (void)hipHostFree(t->result);
     if (t->status_event) (void)hipEventDestroy(t->status_event);
     if (t->side) (void)hipStreamDestroy(t->side);
     if (t->ev_fork) (void)hipEventDestroy(t->ev_fork);
@@ -191,17 +195,18 @@ spt_status ensure_carry(spt_tensor_s* t, int rank) {
         const int64_t nb = std::max<int64_t>(spt::solve_blocks(maxrows), spt::gram_blocks(maxrows));
         if ((st = dalloc(t, &t->M, (size_t)(maxrows * rank), &t->ws_allocs)) != SPT_OK) return st;
         if ((st = dalloc(t, &t->grams, (size_t)(t->N * E), &t->ws_allocs)) != SPT_OK) return st;
-        if ((st = dalloc(t, &t->gpart, (size_t)(nb * E), &t->ws_allocs)) != SPT_OK) return st;
-        if ((st = dalloc(t, &t->ipart, (size_t)(nb * rank), &t->ws_allocs)) != SPT_OK) return st;
+        // block partials and their sums: the Gram's R x R entries, then the R of <M, Y>
+        if ((st = dalloc(t, &t->gpart, (size_t)(nb * (E + rank)), &t->ws_allocs)) != SPT_OK) return st;
+        t->ipart = t->gpart + E;
         if ((st = dalloc(t, &t->Vinv, (size_t)E, &t->ws_allocs)) != SPT_OK) return st;
-        if ((st = dalloc(t, &t->Gsum, (size_t)E, &t->ws_allocs)) != SPT_OK) return st;
+        if ((st = dalloc(t, &t->Gsum, (size_t)(E + rank), &t->ws_allocs)) != SPT_OK) return st;
+        t->Isum = t->Gsum + E;
         for (int w = 0; w < t->N; ++w)
             if ((st = dalloc(t, &t->shadow[w], (size_t)(t->dims[w] * rank), &t->ws_allocs)) != SPT_OK)
                 return st;
-        if ((st = dalloc(t, &t->Isum, (size_t)rank, &t->ws_allocs)) != SPT_OK) return st;
-        if ((st = dalloc(t, &t->fitd, 1, &t->ws_allocs)) != SPT_OK) return st;
-        if ((st = dalloc(t, &t->status, 1, &t->ws_allocs)) != SPT_OK) return st;
-        HIPCHK(hipMemset(t->status, 0, sizeof(int32_t)));
+        // the fit and the sweep's status, copied to the host together
+        if ((st = dalloc(t, &t->fitd, 2, &t->ws_allocs)) != SPT_OK) return st;
+        t->status = (int32_t*)(t->fitd + 1);
     }
     t->ws_rank = rank;
     return SPT_OK;
@@ -828,16 +833,16 @@ spt_status spt_cp_als_iter(spt_tensor_t t, void* const* factors, spt_dtype fdtyp
     if (t->status_pending) {
         HIPCHK(hipEventSynchronize(t->status_event));
         t->status_pending = false;
-        if (t->status_host[0] != 0) {
-            t->status_host[0] = 0;
+        if (t->result->status != 0) {
+            t->result->status = 0;
             return fail(SPT_ERR_NOT_SPD, "normal matrix not positive definite (earlier sweep)");
         }
     }
     spt_status st = ensure_carry(t, rank);
     if (st != SPT_OK) return st;
-    if (!t->status_host) {
-        HIPCHK(hipHostMalloc((void**)&t->status_host, sizeof(int32_t)));
-        t->status_host[0] = 0;
+    if (!t->result) {
+        HIPCHK(hipHostMalloc((void**)&t->result, sizeof(*t->result)));
+        t->result->status = 0;
         HIPCHK(hipEventCreateWithFlags(&t->status_event, hipEventDisableTiming));
     }
     const int N = t->N;
@@ -862,8 +867,7 @@ spt_status spt_cp_als_iter(spt_tensor_t t, void* const* factors, spt_dtype fdtyp
         const int nb = spt::solve_blocks(t->dims[d]);
         spt::launch_solve_rows(rank, t->M, t->Vinv, t->dims[d], (float*)factors[d], t->gpart,
                                t->ipart, s);
-        spt::launch_reduce_partials(t->gpart, nb, (int)E, t->Gsum, s);
-        spt::launch_reduce_partials(t->ipart, nb, rank, t->Isum, s);
+        spt::launch_reduce_partials(t->gpart, nb, (int)(E + rank), t->Gsum, s);
         spt::launch_als_finish(rank, N, d, t->Gsum, t->Isum, t->grams, lambda, t->norm_sq,
                                (fit && d == N - 1) ? 1 : 0, t->fitd, s);
         spt::launch_scale_cols(rank, (float*)factors[d], t->dims[d], lambda, s);
@@ -874,16 +878,15 @@ spt_status spt_cp_als_iter(spt_tensor_t t, void* const* factors, spt_dtype fdtyp
         if ((st = join_side(t, s)) != SPT_OK) return st;
     }
     if (t->copies) t->cur_mode = 0;
-    HIPCHK(hipMemcpyAsync(t->status_host, t->status, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    spt::launch_zero_i32(t->status, 1, s);
+    HIPCHK(hipMemcpyAsync(t->result, t->fitd, sizeof(*t->result), hipMemcpyDeviceToHost, s));
     HIPCHK(hipEventRecord(t->status_event, s));
     t->status_pending = true;
     if (fit) {
-        HIPCHK(hipMemcpyAsync(fit, t->fitd, sizeof(double), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
         t->status_pending = false;
-        if (t->status_host[0] != 0) {
-            t->status_host[0] = 0;
+        *fit = t->result->fit;
+        if (t->result->status != 0) {
+            t->result->status = 0;
             return fail(SPT_ERR_NOT_SPD, "normal matrix not positive definite");
         }
     }

@@ -105,11 +105,12 @@ int gram_blocks(int64_t rows);
 void launch_gram_partial(int rank, const float* Y, int64_t rows, double* partial, hipStream_t s);
 // out[e] = sum_b partial[b][e] (fixed order), e < E
 void launch_reduce_partials(const double* partial, int nblocks, int E, double* out, hipStream_t s);
-// V = Hadamard of grams[w] (w != mode); Cholesky; Vinv.  status[0] |= 1 on
-// failure after one ridge retry.
+// V = Hadamard of grams[w] (w != mode); Cholesky; Vinv.  status[0] = 0 at mode
+// 0, |= 1 on failure after one ridge retry.
 void launch_normal_inverse(int rank, int nmodes, int mode, const double* grams, double* Vinv,
                            int32_t* status, hipStream_t s);
-// Y = M Vinv (FP32 out); partial Grams of Y and partial column sums of M.*Y
+// Y = M Vinv (FP32 out); partial Grams of Y and partial column sums of M.*Y,
+// block b's at gpart + b (R R + R) and ipart + b (R R + R)
 int solve_blocks(int64_t rows);
 void launch_solve_rows(int rank, const float* M, const double* Vinv, int64_t rows, float* Y,
                        double* gpart, double* ipart, hipStream_t s);
@@ -126,7 +127,5 @@ void launch_copy_probe(const void* src, void* dst, int64_t bytes, hipStream_t s)
 // and its device address on the current device (looked up once per device).
 constexpr int64_t kNoAllocScratchBytes = int64_t(16) << 20;
 hipError_t noalloc_scratch(void** ptr);
-// p[0..n) = 0 with a kernel (no memset node when a caller captures a graph)
-void launch_zero_i32(int32_t* p, int n, hipStream_t s);
 
 }  // namespace spt
