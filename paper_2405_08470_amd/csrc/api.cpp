@@ -225,6 +225,13 @@ hipEvent_t mark(spt_tensor_s* t, hipStream_t s) {
     return e;
 }
 
+// Nonzeros from which CP-ALS runs the remap pass on the side stream.  The fork
+// and join between the streams cost about 10 us per mode.
+#ifndef SPT_SIDE_FROM
+#define SPT_SIDE_FROM (2 << 20)
+#endif
+constexpr int64_t kSideRemapFrom = SPT_SIDE_FROM;
+
 spt_status ensure_side(spt_tensor_s* t) {
     if (t->side) return SPT_OK;
     HIPCHK(hipStreamCreateWithFlags(&t->side, hipStreamNonBlocking));  // default priority
@@ -288,7 +295,7 @@ spt_status launch_mode(spt_tensor_s* t, int mode, const uint32_t* rec_in, uint32
         return fail(SPT_ERR_HIP, "launch of the elementwise kernel failed");
     HIPCHK(hipGetLastError());
     tm.ev[1] = mark_if(s);
-    if (staged && als) {
+    if (staged && als && t->nnz >= kSideRemapFrom) {
         spt_status st2 = ensure_side(t);
         if (st2 != SPT_OK) return st2;
         HIPCHK(hipEventRecord(t->ev_fork, s));

@@ -11,13 +11,13 @@
 
 namespace spt {
 
-EcFnPtr pick_ec_n2(int, int, int, int, bool);
-EcFnPtr pick_ec_n3(int, int, int, int, bool);
-EcFnPtr pick_ec_n4(int, int, int, int, bool);
-EcFnPtr pick_ec_n5(int, int, int, int, bool);
-EcFnPtr pick_ec_n6(int, int, int, int, bool);
-EcFnPtr pick_ec_n7(int, int, int, int, bool);
-EcFnPtr pick_ec_n8(int, int, int, int, bool);
+EcFnPtr pick_ec_n2(int, int, int, int, EcForm);
+EcFnPtr pick_ec_n3(int, int, int, int, EcForm);
+EcFnPtr pick_ec_n4(int, int, int, int, EcForm);
+EcFnPtr pick_ec_n5(int, int, int, int, EcForm);
+EcFnPtr pick_ec_n6(int, int, int, int, EcForm);
+EcFnPtr pick_ec_n7(int, int, int, int, EcForm);
+EcFnPtr pick_ec_n8(int, int, int, int, EcForm);
 
 namespace {
 
@@ -95,15 +95,15 @@ __global__ void remap_kernel(const uint32_t* __restrict__ in, uint32_t* __restri
     }
 }
 
-EcFnPtr pick_ec(int nmodes, int rank, int fdtype, int words, int kind, bool reuse) {
+EcFnPtr pick_ec(int nmodes, int rank, int fdtype, int words, int kind, EcForm form) {
     switch (nmodes) {
-        case 2: return pick_ec_n2(rank, fdtype, words, kind, reuse);
-        case 3: return pick_ec_n3(rank, fdtype, words, kind, reuse);
-        case 4: return pick_ec_n4(rank, fdtype, words, kind, reuse);
-        case 5: return pick_ec_n5(rank, fdtype, words, kind, reuse);
-        case 6: return pick_ec_n6(rank, fdtype, words, kind, reuse);
-        case 7: return pick_ec_n7(rank, fdtype, words, kind, reuse);
-        case 8: return pick_ec_n8(rank, fdtype, words, kind, reuse);
+        case 2: return pick_ec_n2(rank, fdtype, words, kind, form);
+        case 3: return pick_ec_n3(rank, fdtype, words, kind, form);
+        case 4: return pick_ec_n4(rank, fdtype, words, kind, form);
+        case 5: return pick_ec_n5(rank, fdtype, words, kind, form);
+        case 6: return pick_ec_n6(rank, fdtype, words, kind, form);
+        case 7: return pick_ec_n7(rank, fdtype, words, kind, form);
+        case 8: return pick_ec_n8(rank, fdtype, words, kind, form);
         default: return nullptr;
     }
 }
@@ -158,23 +158,41 @@ struct EcChoice {
 // - CP-ALS feeds its results back, so a change of rounding grows from sweep to
 //   sweep: its sums stay those of one wave per partition, bit for bit.  There
 //   the reuse form pays only where the partitions fill the chip (4-mode 1e8:
-//   2752-3090 / 2396-2853; 1e6, R 8, 611 partitions: 31-43 / 34-47).
+//   2752-3090 / 2396-2853; 1e6, R 8, 611 partitions: 31-43 / 34-47), and below
+//   2048 partitions the ordered form takes its place (one wave / ordered:
+//   4-mode 2e6, R 64, 977 partitions: 112-147 / 86-115; 1e6, R 8, 611: 35-51 /
+//   26-38; 3-mode 3.5e6, R 32, 1710: 50-52 / 47-48; 5e6, 2442: 69-85 / 85-90;
+//   eight waves up to 256 partitions, 3e5, R 64, 147: 76 / 63; 1e5, R 16, 49:
+//   31 / 26; two above: four gain nothing more at 977 and lose at 1710, 74).
 
 EcChoice choose_ec(int nmodes, int rank, int fdtype, int words, int kind, int kappa, const EcArgs& a) {
-    EcChoice c{pick_ec(nmodes, rank, fdtype, words, kind, false), 1};
-    const EcFnPtr reuse = pick_ec(nmodes, rank, fdtype, words, kind, true);
+    EcChoice c{pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kPlain), 1};
+    const EcFnPtr reuse = pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kReuse);
     if (!c.f || !reuse) return {nullptr, 1};
+#ifdef SPT_EC_ONE_WAVE  // build option: the order of one wave for every caller
+    const bool one_wave = true;
+#else
+    const bool one_wave = a.one_wave != 0;
+#endif
+#ifdef SPT_EC_ORDERED  // build option: partitions below which that order takes the ordered form
+    constexpr int kOrderedBelow = SPT_EC_ORDERED;
+#else
+    constexpr int kOrderedBelow = 2048;
+#endif
+    if (one_wave && !a.rec_out && kappa < kOrderedBelow)
+        if (const EcFnPtr ordered = pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kOrdered))
+            return {ordered, kappa <= 256 ? 8 : 2};
 #ifdef SPT_EC_FORM  // build option: 0 = always the plain form, 1 = always the reuse form
     const bool want = SPT_EC_FORM != 0;
 #else
-    const bool pays = (nmodes >= 4 && !(a.one_wave && kappa < 4096)) || (a.repeats >= 0.4f && kappa >= 4096);
+    const bool pays = (nmodes >= 4 && !(one_wave && kappa < 4096)) || (a.repeats >= 0.4f && kappa >= 4096);
     const bool want = pays && reuse_fits(c.f, reuse, ec_lds_bytes(nmodes, rank, fdtype, 1));
 #endif
     if (want) c.f = reuse;
 #ifdef SPT_EC_WAVES  // build option: waves per partition
     c.waves = SPT_EC_WAVES;
 #else
-    c.waves = a.one_wave ? 1 : kappa <= 256 ? 8 : (!want && kappa >= 8192) ? 1 : 4;
+    c.waves = one_wave ? 1 : kappa <= 256 ? 8 : (!want && kappa >= 8192) ? 1 : 4;
 #endif
     return c;
 }
@@ -182,12 +200,12 @@ EcChoice choose_ec(int nmodes, int rank, int fdtype, int words, int kind, int ka
 }  // namespace
 
 bool pick_ec_exists(int nmodes, int rank, int fdtype, int words, int kind) {
-    return pick_ec(nmodes, rank, fdtype, words, kind, false) != nullptr;
+    return pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kPlain) != nullptr;
 }
 
 bool launch_ec(int nmodes, int rank, int fdtype, int words, int kind, int kappa, const EcArgs& a,
                hipStream_t s) {
-    if (kappa <= 0) return pick_ec(nmodes, rank, fdtype, words, kind, false) != nullptr;
+    if (kappa <= 0) return pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kPlain) != nullptr;
     const EcChoice c = choose_ec(nmodes, rank, fdtype, words, kind, kappa, a);
     if (!c.f) return false;
     EcArgs args = a;

@@ -138,7 +138,44 @@ __device__ __forceinline__ void store_vals(float* dst, const float (&v)[V]) {
 // What a lane group left to the chain combine: a row that starts in it runs on
 // past its sub-range; a row from an earlier group ends in it; ... and ends
 // before the group's last nonzero (the head partial holds its end).
-constexpr int kStarts = 1, kEnds = 2, kHead = 4;
+// (kMoved, during the walk of the ordered form: past the sub-range's first row)
+constexpr int kStarts = 1, kEnds = 2, kHead = 4, kMoved = 8;
+
+// Chain combine: a row that runs on past its group's sub-range is summed in
+// group order by the threads (one per rank) of the group it starts in, whose
+// tail partial opens the chain; a group with no head partial is covered by the
+// row as a whole.  Every chain is walked at once, eight groups' flags and
+// partials read ahead of their use, so a workgroup of many groups waits for
+// its longest row only.
+template <int R>
+__device__ __forceinline__ void combine_chains(const EcArgs& a, const float* part0, const float* part1,
+                                               const int32_t* gflag, const int32_t* prow, const int32_t* pslot,
+                                               int groups) {
+    for (int i = threadIdx.x; i < groups * R; i += blockDim.x) {
+        const int h = i / R, r = i % R;
+        if (!(gflag[h] & kStarts)) continue;
+        float csum = part1[i];
+        bool open = true;
+        for (int k = h + 1; open; k += 8) {
+            int f[8];
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int c = k + j < groups ? k + j : groups - 1;
+                f[j] = gflag[c];
+                v[j] = part1[c * R + r];
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if (open) {
+                    csum += (f[j] & kHead) ? part0[(k + j) * R + r] : v[j];
+                    open = !(f[j] & kEnds);
+                }
+            }
+        }
+        row_dst<R>(a, prow[h], pslot[h])[r] = csum;
+    }
+}
 
 template <int N, int R, typename FT>
 struct EcShape {
@@ -400,36 +437,210 @@ __global__ __launch_bounds__(64 * kEcMaxWaves) void ec_kernel(const EcArgs a) {
     }
     __syncthreads();
 
-    // Chain combine: a row that runs on past its group's sub-range is summed
-    // in group order by the threads (one per rank) of the group it starts in,
-    // whose tail partial opens the chain; a group with no head partial is
-    // covered by the row as a whole.  Every chain is walked at once, eight
-    // groups' flags and partials read ahead of their use, so a workgroup of
-    // many groups waits for its longest row only.
-    for (int i = threadIdx.x; i < SG * R; i += blockDim.x) {
-        const int h = i / R, r = i % R;
-        if (!(gflag[h] & kStarts)) continue;
-        float csum = part1[i];
-        bool open = true;
-        for (int k = h + 1; open; k += 8) {
-            int f[8];
-            float v[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int c = k + j < SG ? k + j : SG - 1;
-                f[j] = gflag[c];
-                v[j] = part1[c * R + r];
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                if (open) {
-                    csum += (f[j] & kHead) ? part0[(k + j) * R + r] : v[j];
-                    open = !(f[j] & kEnds);
+    combine_chains<R>(a, part0, part1, gflag, prow, pslot, SG);
+}
+
+// The sums of one wave per partition, bit for bit, with the gathers of `waves`
+// waves in flight: the partition is split over the G lane groups as one wave
+// splits it, and the waves take turns of B nonzeros per group.  A wave gathers
+// its next turn while the others have theirs; at its turn it adds its products
+// to the groups' running sums, which pass from wave to wave through LDS, with
+// one barrier per turn.  For CP-ALS on tensors whose partitions do not fill the
+// chip, where a lone wave's chain of gathers is the kernel.  Plain form, no
+// remap inside.
+template <int N, int R, int RW, int KIND, typename FT>
+__global__ __launch_bounds__(64 * kEcMaxWaves) void ec_ordered_kernel(const EcArgs a) {
+    using Sh = EcShape<N, R, FT>;
+    constexpr int V = Sh::V, L = Sh::L, G = Sh::G, SW = Sh::SW;
+    constexpr int NG = N - 1;
+    constexpr int BMAX = (SPT_GATHER_INFLIGHT / NG) > 0 ? SPT_GATHER_INFLIGHT / NG : 1;
+    constexpr int B = L <= BMAX ? L : (L / 2 <= BMAX ? L / 2 : (L / 4 <= BMAX ? L / 4 : (L / 8 <= BMAX ? L / 8 : 1)));
+    const int lane = threadIdx.x & 63;
+    const int wv = threadIdx.x >> 6;
+    const int S = a.waves;
+
+    // LDS, within what ec_lds_bytes counts for the waves' own groups
+    HIP_DYNAMIC_SHARED(uint4, smem)
+    float* const part0 = reinterpret_cast<float*>(smem);  // head partials of the groups
+    float* const part1 = part0 + G * R;                   // tail partials
+    float* const sums = part1 + G * R;                    // running sums [64 lanes][V] ...
+    int32_t* const prow = reinterpret_cast<int32_t*>(sums + 64 * V);
+    int32_t* const pslot = prow + G;
+    int32_t* const gflag = pslot + G;
+    int32_t* const crow = gflag + G;                      // ... their rows and slots
+    int32_t* const cslot = crow + G;
+    uint32_t(*const stage)[64] = reinterpret_cast<uint32_t(*)[64]>(cslot + G) + wv * SW;
+    int32_t* const srow = cslot + G + S * SW * 64 + wv * 2 * kEcMaxSplit;
+    int32_t* const sslot = srow + kEcMaxSplit;
+
+    const int z = blockIdx.x;
+    const int g = lane / L;
+    const int li = lane % L;
+    const int64_t s = a.ptr[z];
+    const int64_t n = a.ptr[z + 1] - s;
+    if (n == 0) return;
+    const int sp0 = a.psplit_ptr[z], sp1 = a.psplit_ptr[z + 1];
+    const int nsp = sp1 - sp0;
+    const bool sp_lds = nsp <= kEcMaxSplit;
+    const int mode = a.rot[0];
+    constexpr auto seq = std::make_integer_sequence<int, N>{};
+
+    const int64_t q = n / G, rm = n % G;
+    const int64_t gs = s + g * q + (g < rm ? g : rm);
+    const int gn = (int)(q + (g < rm ? 1 : 0));
+    const int64_t ge = gs + gn;
+    const int rounds = (int)((q + (rm > 0 ? 1 : 0) + B * S - 1) / (B * S));
+
+    Rec<RW> rec;
+    if (li < B && wv * B + li < gn) load_rec<RW>(a.rec_in, gs + wv * B + li, rec);
+    if (sp_lds && lane < nsp) {
+        srow[lane] = a.psplit_row[sp0 + lane];
+        sslot[lane] = a.psplit_slot[sp0 + lane];
+    }
+    // the rows before and after the group's sub-range (every wave fetches them)
+    uint32_t before = 0xFFFFFFFFu, after = 0xFFFFFFFFu;
+    if (gn > 0 && gs > s) {
+        Rec<RW> r;
+        load_rec<RW>(a.rec_in, gs - 1, r);
+        decode_all<RW, KIND>(r, a, stage, lane, seq);
+        before = stage[mode][lane];
+    }
+    if (gn > 0 && ge < s + n) {
+        Rec<RW> r;
+        load_rec<RW>(a.rec_in, ge, r);
+        decode_all<RW, KIND>(r, a, stage, lane, seq);
+        after = stage[mode][lane];
+    }
+    if (wv == 0 && li == 0) {
+        gflag[g] = 0;
+        crow[g] = -1;
+    }
+    auto slot_of = [&](int row) {
+        int slot = -1;
+        if (sp_lds) {
+            for (int j = 0; j < nsp; ++j)
+                if (srow[j] == row) slot = sslot[j];
+        } else {
+            slot = split_slot(a, sp0, sp1, row);
+        }
+        return slot;
+    };
+    wave_sync();
+
+    // stages the turn whose records are in `rec`, issues its gathers and the
+    // next turn's record load
+    uint4 y[B][NG];
+    auto prepare = [&](int step0) {
+        if (li < B && step0 + li < gn) {
+            decode_all<RW, KIND>(rec, a, stage, lane, seq);
+            stage[N][lane] = rword<RW - 1, RW>(rec);
+            stage[N + 1][lane] = (uint32_t)slot_of((int)stage[mode][lane]);
+        }
+        wave_sync();
+        uint32_t rix[B][NG];
+        #pragma unroll
+        for (int b = 0; b < B; ++b)
+            #pragma unroll
+            for (int k = 0; k < NG; ++k) rix[b][k] = stage[a.rot[k + 1]][g * L + b];
+        #pragma unroll
+        for (int b = 0; b < B; ++b)
+            #pragma unroll
+            for (int k = 0; k < NG; ++k)
+                // a nonzero past the group's range gathers row 0
+                y[b][k] = *reinterpret_cast<const uint4*>(
+                    static_cast<const char*>(a.fac[k + 1]) +
+                    ((int64_t)(step0 + b < gn ? rix[b][k] : 0u) * R + li * V) * FT::kBytes);
+        if (li < B && step0 + S * B + li < gn) load_rec<RW>(a.rec_in, gs + step0 + S * B + li, rec);
+    };
+    prepare(wv * B);
+    __syncthreads();
+
+    for (int t = 0; t < rounds; ++t) {
+        const int step0 = (t * S + wv) * B;
+        const int cnt = gn - step0;
+        for (int w = 0; w < S; ++w) {
+            if (w == wv) {
+                int cur_row = crow[g], cur_slot = cslot[g], flags = gflag[g];
+                float acc[V];
+                #pragma unroll
+                for (int v = 0; v < V; ++v) acc[v] = sums[lane * V + v];
+                #pragma unroll
+                for (int j = 0; j < B; ++j) {
+                    if (j < cnt) {
+                        const int slot = g * L + j;
+                        const int row = (int)stage[mode][slot];
+                        if (row != cur_row) {
+                            if (cur_row >= 0) {
+                                // the sub-range's first row, begun in an earlier group
+                                if (!(flags & kMoved) && before == (uint32_t)cur_row) {
+                                    store_vals<V>(part0 + g * R + li * V, acc);
+                                    flags |= kHead;
+                                    if (li == 0) prow[g] = cur_row;  // (keeps the two stores apart)
+                                } else {
+                                    store_vals<V>(row_dst<R>(a, cur_row, cur_slot) + li * V, acc);
+                                }
+                                flags |= kMoved;
+                            }
+                            cur_row = row;
+                            cur_slot = (int)stage[N + 1][slot];
+                            #pragma unroll
+                            for (int v = 0; v < V; ++v) acc[v] = 0.0f;
+                        }
+                        const float val = __uint_as_float(stage[N][slot]);
+                        float prod[V];
+                        widen<FT>(y[j][0], prod);
+                        #pragma unroll
+                        for (int k = 1; k < NG; ++k) {
+                            float f[V];
+                            widen<FT>(y[j][k], f);
+                            #pragma unroll
+                            for (int v = 0; v < V; ++v) prod[v] *= f[v];
+                        }
+                        #pragma unroll
+                        for (int v = 0; v < V; ++v) acc[v] = fmaf(prod[v], val, acc[v]);
+                    }
+                }
+                #pragma unroll
+                for (int v = 0; v < V; ++v) sums[lane * V + v] = acc[v];
+                wave_sync();
+                if (li == 0) {
+                    crow[g] = cur_row;
+                    cslot[g] = cur_slot;
+                    gflag[g] = flags;
                 }
             }
+            __syncthreads();
+            if (w == wv && t + 1 < rounds) prepare(step0 + S * B);
         }
-        row_dst<R>(a, prow[h], pslot[h])[r] = csum;
     }
+
+    // the groups' last segments, by the first wave
+    if (wv == 0) {
+        const int cur_row = crow[g], cur_slot = cslot[g], flags = gflag[g];
+        float acc[V];
+        #pragma unroll
+        for (int v = 0; v < V; ++v) acc[v] = sums[lane * V + v];
+        const bool open_right = cur_row >= 0 && after == (uint32_t)cur_row;
+        const bool cont = !(flags & kMoved) && before == (uint32_t)cur_row;
+        if (cur_row >= 0) {
+            if (open_right || cont) {
+                store_vals<V>(part1 + g * R + li * V, acc);
+                if (li == 0) {
+                    prow[g] = cur_row;
+                    pslot[g] = cur_slot;
+                }
+            } else {
+                store_vals<V>(row_dst<R>(a, cur_row, cur_slot) + li * V, acc);
+            }
+        }
+        wave_sync();
+        if (li == 0) {
+            const int head = flags & kHead;
+            gflag[g] = head | (open_right && !cont ? kStarts : 0) | (head || !open_right ? kEnds : 0);
+        }
+    }
+    __syncthreads();
+    combine_chains<R>(a, part0, part1, gflag, prow, pslot, G);
 }
 
 using EcFn = EcFnPtr;
@@ -457,33 +668,52 @@ EcFn pick_rank(int rank, int fdtype) {
 }
 
 template <int N, int RW, int KIND>
-EcFn pick_rank(int rank, int fdtype, bool reuse) {
-    return reuse ? pick_rank<N, RW, KIND, true>(rank, fdtype) : pick_rank<N, RW, KIND, false>(rank, fdtype);
+EcFn pick_ordered(int rank, int fdtype) {
+    switch (rank) {  // the ranks of CP-ALS
+        case 8: return fdtype == 0 ? ec_ordered_kernel<N, 8, RW, KIND, FacF32> : ec_ordered_kernel<N, 8, RW, KIND, FacBF16>;
+        case 16: return fdtype == 0 ? ec_ordered_kernel<N, 16, RW, KIND, FacF32> : ec_ordered_kernel<N, 16, RW, KIND, FacBF16>;
+        case 32: return fdtype == 0 ? ec_ordered_kernel<N, 32, RW, KIND, FacF32> : ec_ordered_kernel<N, 32, RW, KIND, FacBF16>;
+        case 64: return fdtype == 0 ? ec_ordered_kernel<N, 64, RW, KIND, FacF32> : ec_ordered_kernel<N, 64, RW, KIND, FacBF16>;
+        default: return nullptr;
+    }
+}
+
+// (the ordered form exists for the 12-byte records the library chooses by itself)
+template <int N, int RW, int KIND>
+EcFn pick_rank(int rank, int fdtype, EcForm form) {
+    if (form == EcForm::kOrdered) {
+        if constexpr (RW == 3)
+            return pick_ordered<N, RW, KIND>(rank, fdtype);
+        else
+            return nullptr;
+    }
+    return form == EcForm::kReuse ? pick_rank<N, RW, KIND, true>(rank, fdtype)
+                                  : pick_rank<N, RW, KIND, false>(rank, fdtype);
 }
 
 // (record words, layout kind) pairs the planner can choose for N modes
 template <int N>
-EcFn pick_layout(int rank, int fdtype, int words, int kind, bool reuse) {
+EcFn pick_layout(int rank, int fdtype, int words, int kind, EcForm form) {
     if constexpr (N <= 2) {
-        if (words == 3 && kind == kWord32) return pick_rank<N, 3, kWord32>(rank, fdtype, reuse);
-        if (words == 4 && kind == kWord32) return pick_rank<N, 4, kWord32>(rank, fdtype, reuse);
+        if (words == 3 && kind == kWord32) return pick_rank<N, 3, kWord32>(rank, fdtype, form);
+        if (words == 4 && kind == kWord32) return pick_rank<N, 4, kWord32>(rank, fdtype, form);
     } else if constexpr (N == 3) {
-        if (words == 3 && kind == kPacked) return pick_rank<N, 3, kPacked>(rank, fdtype, reuse);
-        if (words == 4 && kind == kWord32) return pick_rank<N, 4, kWord32>(rank, fdtype, reuse);
+        if (words == 3 && kind == kPacked) return pick_rank<N, 3, kPacked>(rank, fdtype, form);
+        if (words == 4 && kind == kWord32) return pick_rank<N, 4, kWord32>(rank, fdtype, form);
     } else if constexpr (N <= 6) {
         if constexpr (N == 4)
-            if (words == 3 && kind == kHalf16) return pick_rank<N, 3, kHalf16>(rank, fdtype, reuse);
-        if (words == 3 && kind == kPacked) return pick_rank<N, 3, kPacked>(rank, fdtype, reuse);
-        if (words == 4 && kind == kHalf16) return pick_rank<N, 4, kHalf16>(rank, fdtype, reuse);
-        if (words == 4 && kind == kPacked) return pick_rank<N, 4, kPacked>(rank, fdtype, reuse);
-        if (words == 8 && kind == kWord32) return pick_rank<N, 8, kWord32>(rank, fdtype, reuse);
+            if (words == 3 && kind == kHalf16) return pick_rank<N, 3, kHalf16>(rank, fdtype, form);
+        if (words == 3 && kind == kPacked) return pick_rank<N, 3, kPacked>(rank, fdtype, form);
+        if (words == 4 && kind == kHalf16) return pick_rank<N, 4, kHalf16>(rank, fdtype, form);
+        if (words == 4 && kind == kPacked) return pick_rank<N, 4, kPacked>(rank, fdtype, form);
+        if (words == 8 && kind == kWord32) return pick_rank<N, 8, kWord32>(rank, fdtype, form);
     } else if constexpr (N == 7) {
-        if (words == 3 && kind == kPacked) return pick_rank<N, 3, kPacked>(rank, fdtype, reuse);
-        if (words == 8 && kind == kWord32) return pick_rank<N, 8, kWord32>(rank, fdtype, reuse);
+        if (words == 3 && kind == kPacked) return pick_rank<N, 3, kPacked>(rank, fdtype, form);
+        if (words == 8 && kind == kWord32) return pick_rank<N, 8, kWord32>(rank, fdtype, form);
     } else {
-        if (words == 3 && kind == kPacked) return pick_rank<N, 3, kPacked>(rank, fdtype, reuse);
-        if (words == 8 && kind == kHalf16) return pick_rank<N, 8, kHalf16>(rank, fdtype, reuse);
-        if (words == 12 && kind == kWord32) return pick_rank<N, 12, kWord32>(rank, fdtype, reuse);
+        if (words == 3 && kind == kPacked) return pick_rank<N, 3, kPacked>(rank, fdtype, form);
+        if (words == 8 && kind == kHalf16) return pick_rank<N, 8, kHalf16>(rank, fdtype, form);
+        if (words == 12 && kind == kWord32) return pick_rank<N, 12, kWord32>(rank, fdtype, form);
     }
     return nullptr;
 }

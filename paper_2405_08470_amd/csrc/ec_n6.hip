@@ -4,8 +4,8 @@
 
 namespace spt {
 
-EcFnPtr pick_ec_n6(int rank, int fdtype, int words, int kind, bool reuse) {
-    return pick_layout<6>(rank, fdtype, words, kind, reuse);
+EcFnPtr pick_ec_n6(int rank, int fdtype, int words, int kind, EcForm form) {
+    return pick_layout<6>(rank, fdtype, words, kind, form);
 }
 
 }  // namespace spt

@@ -55,6 +55,11 @@ struct FixupArgs {
 
 using EcFnPtr = void (*)(EcArgs);
 
+// Forms of the elementwise kernel: every nonzero gathers all its rows; the
+// last gathered row is kept over a run of nonzeros that share it; several
+// waves that add in the order of one.
+enum class EcForm { kPlain, kReuse, kOrdered };
+
 // Waves per workgroup the elementwise kernel is compiled for.
 constexpr int kEcMaxWaves = 8;
 // Split rows of a partition the elementwise kernel keeps in LDS.

@@ -43,15 +43,13 @@ SHAPES = [
 ]
 
 
-@pytest.fixture(scope="module", params=[(1, 1), (4, 0), (8, 1)], ids=lambda p: f"waves{p[0]}form{p[1]}")
-def split_lib(request, lib, tmp_path_factory):  # noqa: F811
+def _build(lib, tmp_path_factory, defines):  # noqa: F811
     import ctypes
     import subprocess
-    waves, form = request.param
     out = tmp_path_factory.mktemp("split")
     flags = ["-std=c++17", "-O1", "-g", "-fPIC", "-I", K.HERE, "-I", os.path.join(K.ROOT, "include"), "-I", K.CSRC]
     o, so = str(out / "ec_kernel.o"), str(out / "lib.so")
-    subprocess.run([K.CXX, *flags, f"-DSPT_EC_WAVES={waves}", f"-DSPT_EC_FORM={form}", "-x", "c++", "-c",
+    subprocess.run([K.CXX, *flags, *[f"-D{d}" for d in defines], "-x", "c++", "-c",
                     os.path.join(K.CSRC, "ec_kernel.hip"), "-o", o], check=True, capture_output=True)
     objs = dict(K._OBJS, **{"ec_kernel.o": o})
     subprocess.run([K.CXX, "-shared", "-o", so, *objs.values(), "-pthread"], check=True, capture_output=True)
@@ -60,6 +58,17 @@ def split_lib(request, lib, tmp_path_factory):  # noqa: F811
         getattr(L, name).argtypes = getattr(lib, name).argtypes
     L.spt_last_error.restype = ctypes.c_char_p
     return L
+
+
+@pytest.fixture(scope="module", params=[(1, 1), (4, 0), (8, 1)], ids=lambda p: f"waves{p[0]}form{p[1]}")
+def split_lib(request, lib, tmp_path_factory):  # noqa: F811
+    return _build(lib, tmp_path_factory, [f"SPT_EC_WAVES={request.param[0]}", f"SPT_EC_FORM={request.param[1]}"])
+
+
+@pytest.fixture(scope="module")
+def order_libs(lib, tmp_path_factory):  # noqa: F811
+    """The order of one wave: by one wave, and by the ordered form's turns."""
+    return [_build(lib, tmp_path_factory, ["SPT_EC_ONE_WAVE", f"SPT_EC_ORDERED={below}"]) for below in (0, 1 << 30)]
 
 
 @pytest.mark.parametrize("lib", ["chosen"], indirect=True)  # (only its objects are used)
@@ -76,3 +85,27 @@ def test_split_of_a_partition(lib, split_lib, shape, bf16):  # noqa: F811
         ref = oracle.mttkrp(dims, idx, val, exact, d)
         check_elementwise(out, ref, mttkrp_abs(dims, idx, val, exact, d), label=f"{name} mode {d}")
     t.free()
+
+
+@pytest.mark.parametrize("lib", ["chosen"], indirect=True)
+@pytest.mark.parametrize("shape", SHAPES + [("four_modes", synth.random_coo, 64, 3), ("kappa300", synth.random_coo, 16, 300)],
+                         ids=lambda s: s[0])
+@pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
+def test_ordered_form_gives_the_bits_of_one_wave(lib, order_libs, shape, bf16):  # noqa: F811
+    name, made, R, kappa = shape
+    if callable(made):
+        dims = (60, 50, 40, 7) if name == "four_modes" else (60, 50, 40)
+        idx = made(dims, 6000, seed=3, dist="zipf", zipf_s=1.1)[0]
+    else:
+        dims, idx = made
+    if R > 64:
+        R = 64  # CP-ALS ranks
+    val = synth.normal(3, 1, idx.shape[1]).astype(np.float32)
+    Y = [bf16_bits(y) if bf16 else y for y in synth.random_factors(dims, R, seed=18)]
+    outs = []
+    for L in order_libs:
+        t = T(L, dims, idx, val, kappa=kappa)
+        outs.append([t.mttkrp(d, Y, R, bf16=bf16) for d in range(len(dims))])
+        t.free()
+    for one, ordered in zip(*outs):
+        assert np.array_equal(one.view(np.uint32), ordered.view(np.uint32)), name

@@ -60,3 +60,37 @@ def test_split_of_partitions(name, shape, R, kappa, dtype):
         ref = oracle.mttkrp(dims, idx, val, exact, d)
         check_elementwise(out.cpu().numpy(), ref, mttkrp_abs(dims, idx, val, exact, d), label=f"{name} mode {d}")
     t.free()
+
+
+ALS = [
+    # name, dims, nnz, rank, kappa (8 waves in turn up to 256, 2 up to 2047, then one), wide layout
+    ("three_modes", (300, 200, 4000), 60_000, 16, 49, "word32"),
+    ("kappa256", (300, 200, 4000), 60_000, 32, 256, "word32"),
+    ("kappa257", (300, 200, 4000), 60_000, 32, 257, "word32"),
+    ("kappa2047", (300, 200, 4000), 60_000, 8, 2047, "word32"),
+    ("kappa2048", (300, 200, 4000), 60_000, 8, 2048, "word32"),
+    ("four_modes", (300, 200, 400, 90), 60_000, 64, 300, "half16"),
+    ("one_partition", (300, 200, 400, 90), 9_000, 64, 1, "half16"),
+]
+
+
+@pytest.mark.parametrize("name,dims,nnz,R,kappa,wide", ALS, ids=[c[0] for c in ALS])
+@pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
+def test_als_sums_keep_the_order_of_one_wave(name, dims, nnz, R, kappa, wide, bf16):
+    """Wide records have no ordered form: one wave per partition computes them.
+    The same sweep on 12-byte records must give the same bits."""
+    print("case", name, bf16, flush=True)
+    idx, val = synth.random_coo(dims, nnz, seed=5, dist="zipf", zipf_s=0.7)
+    Y = synth.random_factors(dims, R, seed=18)
+    res = []
+    for layout in ("auto", wide):
+        t = S.tensor_load_coo(dims, idx, val, kappa=kappa, prep="device", layout=layout)
+        f = [torch.from_numpy(y).cuda() for y in Y]
+        lam = torch.empty(R, dtype=torch.float64, device="cuda")
+        fits = [S.cp_als_iter(t, f, lam, bf16_gather=bf16) for _ in range(2)]
+        res.append((fits, lam.cpu().numpy(), [x.cpu().numpy() for x in f]))
+        t.free()
+    assert res[0][0] == res[1][0]
+    assert np.array_equal(res[0][1], res[1][1])
+    for a, b in zip(res[0][2], res[1][2]):
+        assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
