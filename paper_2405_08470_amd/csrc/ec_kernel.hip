@@ -11,13 +11,13 @@
 
 namespace spt {
 
-EcFnPtr pick_ec_n2(int, int, int, int, EcForm);
-EcFnPtr pick_ec_n3(int, int, int, int, EcForm);
-EcFnPtr pick_ec_n4(int, int, int, int, EcForm);
-EcFnPtr pick_ec_n5(int, int, int, int, EcForm);
-EcFnPtr pick_ec_n6(int, int, int, int, EcForm);
-EcFnPtr pick_ec_n7(int, int, int, int, EcForm);
-EcFnPtr pick_ec_n8(int, int, int, int, EcForm);
+EcFnPtr pick_ec_n2(int, int, int, int, EcForm, bool);
+EcFnPtr pick_ec_n3(int, int, int, int, EcForm, bool);
+EcFnPtr pick_ec_n4(int, int, int, int, EcForm, bool);
+EcFnPtr pick_ec_n5(int, int, int, int, EcForm, bool);
+EcFnPtr pick_ec_n6(int, int, int, int, EcForm, bool);
+EcFnPtr pick_ec_n7(int, int, int, int, EcForm, bool);
+EcFnPtr pick_ec_n8(int, int, int, int, EcForm, bool);
 
 namespace {
 
@@ -95,15 +95,15 @@ __global__ void remap_kernel(const uint32_t* __restrict__ in, uint32_t* __restri
     }
 }
 
-EcFnPtr pick_ec(int nmodes, int rank, int fdtype, int words, int kind, EcForm form) {
+EcFnPtr pick_ec(int nmodes, int rank, int fdtype, int words, int kind, EcForm form, bool longer = false) {
     switch (nmodes) {
-        case 2: return pick_ec_n2(rank, fdtype, words, kind, form);
-        case 3: return pick_ec_n3(rank, fdtype, words, kind, form);
-        case 4: return pick_ec_n4(rank, fdtype, words, kind, form);
-        case 5: return pick_ec_n5(rank, fdtype, words, kind, form);
-        case 6: return pick_ec_n6(rank, fdtype, words, kind, form);
-        case 7: return pick_ec_n7(rank, fdtype, words, kind, form);
-        case 8: return pick_ec_n8(rank, fdtype, words, kind, form);
+        case 2: return pick_ec_n2(rank, fdtype, words, kind, form, longer);
+        case 3: return pick_ec_n3(rank, fdtype, words, kind, form, longer);
+        case 4: return pick_ec_n4(rank, fdtype, words, kind, form, longer);
+        case 5: return pick_ec_n5(rank, fdtype, words, kind, form, longer);
+        case 6: return pick_ec_n6(rank, fdtype, words, kind, form, longer);
+        case 7: return pick_ec_n7(rank, fdtype, words, kind, form, longer);
+        case 8: return pick_ec_n8(rank, fdtype, words, kind, form, longer);
         default: return nullptr;
     }
 }
@@ -135,6 +135,7 @@ bool reuse_fits(EcFnPtr plain, EcFnPtr reuse, size_t lds) {
 struct EcChoice {
     EcFnPtr f;
     int waves;
+    bool longer;  // steps of more records
 };
 
 // Where the lines lie (MI355X, us per launch, plain / reuse form unless said):
@@ -166,9 +167,10 @@ struct EcChoice {
 //   31 / 26; two above: four gain nothing more at 977 and lose at 1710, 74).
 
 EcChoice choose_ec(int nmodes, int rank, int fdtype, int words, int kind, int kappa, const EcArgs& a) {
-    EcChoice c{pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kPlain), 1};
-    const EcFnPtr reuse = pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kReuse);
-    if (!c.f || !reuse) return {nullptr, 1};
+    const bool longer = a.nnz / kappa >= 4096;
+    EcChoice c{pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kPlain, longer), 1, longer};
+    const EcFnPtr reuse = pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kReuse, longer);
+    if (!c.f || !reuse) return {nullptr, 1, false};
 #ifdef SPT_EC_ONE_WAVE  // build option: the order of one wave for every caller
     const bool one_wave = true;
 #else
@@ -181,12 +183,12 @@ EcChoice choose_ec(int nmodes, int rank, int fdtype, int words, int kind, int ka
 #endif
     if (one_wave && !a.rec_out && kappa < kOrderedBelow)
         if (const EcFnPtr ordered = pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kOrdered))
-            return {ordered, kappa <= 256 ? 8 : 2};
+            return {ordered, kappa <= 256 ? 8 : 2, false};
 #ifdef SPT_EC_FORM  // build option: 0 = always the plain form, 1 = always the reuse form
     const bool want = SPT_EC_FORM != 0;
 #else
     const bool pays = (nmodes >= 4 && !(one_wave && kappa < 4096)) || (a.repeats >= 0.4f && kappa >= 4096);
-    const bool want = pays && reuse_fits(c.f, reuse, ec_lds_bytes(nmodes, rank, fdtype, 1));
+    const bool want = pays && reuse_fits(c.f, reuse, ec_lds_bytes(nmodes, rank, fdtype, 1, longer));
 #endif
     if (want) c.f = reuse;
 #ifdef SPT_EC_WAVES  // build option: waves per partition
@@ -210,8 +212,11 @@ bool launch_ec(int nmodes, int rank, int fdtype, int words, int kind, int kappa,
     if (!c.f) return false;
     EcArgs args = a;
     args.waves = c.waves;
+    // LDS of one workgroup stays within 64 KB (8 modes at rank 8 with BF16
+    // factors need 68 KB for 8 waves)
+    while (args.waves > 2 && ec_lds_bytes(nmodes, rank, fdtype, args.waves, c.longer) > 65536) args.waves /= 2;
     hipLaunchKernelGGL(c.f, dim3((unsigned)kappa), dim3((unsigned)(64 * args.waves)),
-                       (size_t)ec_lds_bytes(nmodes, rank, fdtype, args.waves), s, args);
+                       (size_t)ec_lds_bytes(nmodes, rank, fdtype, args.waves, c.longer), s, args);
     return true;
 }
 

@@ -67,10 +67,11 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int RW, int KIND, int... W>
-__device__ __forceinline__ void decode_all(const Rec<RW>& r, const EcArgs& a, uint32_t (*st)[64],
-                                           int lane, std::integer_sequence<int, W...>) {
-    ((st[W][lane] = decode<W, RW, KIND>(r, a)), ...);
+// The record's indices into column `at` of the staging rows st[mode].
+template <int RW, int KIND, int WIDTH, int... W>
+__device__ __forceinline__ void decode_all(const Rec<RW>& r, const EcArgs& a, uint32_t (*st)[WIDTH],
+                                           int at, std::integer_sequence<int, W...>) {
+    ((st[W][at] = decode<W, RW, KIND>(r, a)), ...);
 }
 
 // Carry slot of `row` if it is a split row of this partition, else -1.
@@ -185,18 +186,20 @@ struct EcShape {
     static constexpr int SW = N + 2;     // staged words per nonzero: indices in mode order, value, carry slot
 };
 
-template <int N, int R, int RW, int KIND, typename FT, bool REUSE>
+template <int N, int R, int RW, int KIND, typename FT, bool REUSE, bool LONGER>
 __global__ __launch_bounds__(64 * kEcMaxWaves) void ec_kernel(const EcArgs a) {
     using Sh = EcShape<N, R, FT>;
     constexpr int V = Sh::V;
     constexpr int L = Sh::L;
     constexpr int G = Sh::G;
     constexpr int NG = N - 1;    // gathered factor rows per nonzero
-    // nonzeros whose gathers are issued together: the largest divisor of L
-    // with at most SPT_GATHER_INFLIGHT float4 gathers in flight per lane
+    constexpr int K = ec_step_records(R, FT::kBytes == 2, LONGER);  // records a lane stages per step
+    constexpr int J = K * L;     // nonzeros per group and step
+    // nonzeros whose gathers are issued together: the largest power-of-two
+    // part of J with at most SPT_GATHER_INFLIGHT float4 gathers in flight per lane
     constexpr int BMAX = (SPT_GATHER_INFLIGHT / NG) > 0 ? SPT_GATHER_INFLIGHT / NG : 1;
-    constexpr int B = L <= BMAX ? L : (L / 2 <= BMAX ? L / 2 : (L / 4 <= BMAX ? L / 4 : (L / 8 <= BMAX ? L / 8 : 1)));
-    static_assert(R % V == 0 && L >= 1 && 64 % L == 0 && L % B == 0, "rank");
+    constexpr int B = J <= BMAX ? J : (J / 2 <= BMAX ? J / 2 : (J / 4 <= BMAX ? J / 4 : (J / 8 <= BMAX ? J / 8 : 1)));
+    static_assert(R % V == 0 && L >= 1 && 64 % L == 0 && J % B == 0, "rank");
     constexpr int SW = Sh::SW;
     constexpr int MAXSPLIT = kEcMaxSplit;
 
@@ -208,8 +211,8 @@ __global__ __launch_bounds__(64 * kEcMaxWaves) void ec_kernel(const EcArgs a) {
     HIP_DYNAMIC_SHARED(uint4, smem)
     float* const part0 = reinterpret_cast<float*>(smem);  // head partials of the groups
     float* const part1 = part0 + SG * R;                  // tail partials
-    uint32_t(*const stage)[64] = reinterpret_cast<uint32_t(*)[64]>(part1 + SG * R) + wv * SW;
-    int32_t* const prow = reinterpret_cast<int32_t*>(part1 + SG * R) + a.waves * SW * 64;  // row of the tail partial
+    uint32_t(*const stage)[64 * K] = reinterpret_cast<uint32_t(*)[64 * K]>(part1 + SG * R) + wv * SW;
+    int32_t* const prow = reinterpret_cast<int32_t*>(part1 + SG * R) + a.waves * SW * 64 * K;  // row of the tail partial
     int32_t* const pslot = prow + SG;        // its carry slot
     int32_t* const gflag = pslot + SG;       // after the walk: kStarts, kEnds, kHead
     uint32_t(*const brow)[2] = reinterpret_cast<uint32_t(*)[2]>(gflag + SG);  // rows before and after a sub-range
@@ -237,12 +240,21 @@ __global__ __launch_bounds__(64 * kEcMaxWaves) void ec_kernel(const EcArgs a) {
     // The first records, the rows on either side of the group's sub-range and
     // the split rows are fetched together: one round trip before the walk.
     const bool remap_inline = a.rec_out != nullptr;
-    Rec<RW> ra, rb;
-    int32_t na = 0, nb = 0;
-    if (li < gn) {
-        load_rec<RW>(a.rec_in, gs + li, ra);
-        if (remap_inline) na = a.nxt[gs + li];
-    }
+    // the records of one step: lane li takes nonzeros li, L + li, ... of its group
+    struct Step {
+        Rec<RW> rec[K];
+        int32_t nxt[K];
+    };
+    Step sa, sb;
+    auto fetch = [&](int step0, Step& to) {
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (step0 + k * L + li < gn) {
+                load_rec<RW>(a.rec_in, gs + step0 + k * L + li, to.rec[k]);
+                if (remap_inline) to.nxt[k] = a.nxt[gs + step0 + k * L + li];
+            }
+    };
+    fetch(0, sa);
     if (sp_lds && lane < nsp) {
         srow[lane] = a.psplit_row[sp0 + lane];
         sslot[lane] = a.psplit_slot[sp0 + lane];
@@ -292,24 +304,27 @@ __global__ __launch_bounds__(64 * kEcMaxWaves) void ec_kernel(const EcArgs a) {
     // the first gathers, then run the lane groups over their L nonzeros of
     // this step.  Two record buffers alternate, so a prefetch never
     // overwrites the registers of a remap store still in flight.
-    auto step = [&](int step0, Rec<RW>& cur, int32_t& ncur, Rec<RW>& nxt_rec, int32_t& nnext) {
-        if (step0 + li < gn) {
-            if (remap_inline) store_rec<RW>(a.rec_out, ncur, cur);
-            decode_all<RW, KIND>(cur, a, stage, lane, seq);
-            stage[N][lane] = rword<RW - 1, RW>(cur);
-            stage[N + 1][lane] = (uint32_t)slot_of((int)stage[mode][lane]);
-        }
+    auto step = [&](int step0, Step& cur, Step& next) {
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (step0 + k * L + li < gn) {
+                const int at = k * 64 + lane;
+                if (remap_inline) store_rec<RW>(a.rec_out, cur.nxt[k], cur.rec[k]);
+                decode_all<RW, KIND>(cur.rec[k], a, stage, at, seq);
+                stage[N][at] = rword<RW - 1, RW>(cur.rec[k]);
+                stage[N + 1][at] = (uint32_t)slot_of((int)stage[mode][at]);
+            }
         wave_sync();
         const int cnt = gn - step0;
         #pragma unroll
-        for (int kb = 0; kb < L; kb += B) {
+        for (int kb = 0; kb < J; kb += B) {
             // the batch's rows first (one LDS wait for all of them), then its
             // gathers back to back; a nonzero past the group's range gathers
             // row 0 (always a valid row) instead of branching around the load
             uint32_t orow[B], rix[B][NG];
             #pragma unroll
             for (int b = 0; b < B; ++b) {
-                const int slot = gl * L + kb + b;
+                const int slot = (kb + b) / L * 64 + gl * L + (kb + b) % L;
                 orow[b] = stage[mode][slot];
                 #pragma unroll
                 for (int k = 0; k < NG; ++k) rix[b][k] = stage[a.rot[k + 1]][slot];
@@ -340,14 +355,11 @@ __global__ __launch_bounds__(64 * kEcMaxWaves) void ec_kernel(const EcArgs a) {
                     }
                 }
             }
-            if (kb == 0 && step0 + L + li < gn) {
-                load_rec<RW>(a.rec_in, gs + step0 + L + li, nxt_rec);
-                if (remap_inline) nnext = a.nxt[gs + step0 + L + li];
-            }
+            if (kb == 0) fetch(step0 + J, next);
             #pragma unroll
             for (int b = 0; b < B; ++b) {
                 if (kb + b < cnt) {
-                    const int slot = gl * L + kb + b;
+                    const int slot = (kb + b) / L * 64 + gl * L + (kb + b) % L;
                     const int row = (int)orow[b];
                     if (REUSE && fresh[b]) {
                         widen<FT>(y[b][NG - 1], ylast);
@@ -412,9 +424,9 @@ __global__ __launch_bounds__(64 * kEcMaxWaves) void ec_kernel(const EcArgs a) {
         }
         wave_sync();
     };
-    for (int t = 0; t < steps; t += 2 * L) {
-        step(t, ra, na, rb, nb);
-        if (t + L < steps) step(t + L, rb, nb, ra, na);
+    for (int t = 0; t < steps; t += 2 * J) {
+        step(t, sa, sb);
+        if (t + J < steps) step(t + J, sb, sa);
     }
 
     // the group's last segment
@@ -645,24 +657,22 @@ __global__ __launch_bounds__(64 * kEcMaxWaves) void ec_ordered_kernel(const EcAr
 
 using EcFn = EcFnPtr;
 
-template <int N, int RW, int KIND, bool REUSE>
-EcFn pick_rank(int rank, int fdtype) {
-    if (fdtype == 0) {
-        switch (rank) {
-            case 8: return ec_kernel<N, 8, RW, KIND, FacF32, REUSE>;
-            case 16: return ec_kernel<N, 16, RW, KIND, FacF32, REUSE>;
-            case 32: return ec_kernel<N, 32, RW, KIND, FacF32, REUSE>;
-            case 64: return ec_kernel<N, 64, RW, KIND, FacF32, REUSE>;
-            case 128: return ec_kernel<N, 128, RW, KIND, FacF32, REUSE>;
-            default: return nullptr;
-        }
-    }
+// (longer steps exist where a nonzero has 4 lanes)
+template <int N, int R, int RW, int KIND, typename FT, bool REUSE>
+EcFn pick_steps(bool longer) {
+    if constexpr (ec_step_records(R, FT::kBytes == 2, true) != ec_step_records(R, FT::kBytes == 2, false))
+        if (longer) return ec_kernel<N, R, RW, KIND, FT, REUSE, true>;
+    return ec_kernel<N, R, RW, KIND, FT, REUSE, false>;
+}
+
+template <int N, int RW, int KIND, typename FT, bool REUSE>
+EcFn pick_rank(int rank, bool longer) {
     switch (rank) {
-        case 8: return ec_kernel<N, 8, RW, KIND, FacBF16, REUSE>;
-        case 16: return ec_kernel<N, 16, RW, KIND, FacBF16, REUSE>;
-        case 32: return ec_kernel<N, 32, RW, KIND, FacBF16, REUSE>;
-        case 64: return ec_kernel<N, 64, RW, KIND, FacBF16, REUSE>;
-        case 128: return ec_kernel<N, 128, RW, KIND, FacBF16, REUSE>;
+        case 8: return pick_steps<N, 8, RW, KIND, FT, REUSE>(longer);
+        case 16: return pick_steps<N, 16, RW, KIND, FT, REUSE>(longer);
+        case 32: return pick_steps<N, 32, RW, KIND, FT, REUSE>(longer);
+        case 64: return pick_steps<N, 64, RW, KIND, FT, REUSE>(longer);
+        case 128: return pick_steps<N, 128, RW, KIND, FT, REUSE>(longer);
         default: return nullptr;
     }
 }
@@ -678,42 +688,44 @@ EcFn pick_ordered(int rank, int fdtype) {
     }
 }
 
-// (the ordered form exists for the 12-byte records the library chooses by itself)
 template <int N, int RW, int KIND>
-EcFn pick_rank(int rank, int fdtype, EcForm form) {
-    if (form == EcForm::kOrdered) {
+EcFn pick_form(int rank, int fdtype, EcForm form, bool longer) {
+    if (form == EcForm::kOrdered) {  // for the 12-byte records the library chooses by itself
         if constexpr (RW == 3)
             return pick_ordered<N, RW, KIND>(rank, fdtype);
         else
             return nullptr;
     }
-    return form == EcForm::kReuse ? pick_rank<N, RW, KIND, true>(rank, fdtype)
-                                  : pick_rank<N, RW, KIND, false>(rank, fdtype);
+    if (form == EcForm::kReuse)
+        return fdtype == 0 ? pick_rank<N, RW, KIND, FacF32, true>(rank, longer)
+                           : pick_rank<N, RW, KIND, FacBF16, true>(rank, longer);
+    return fdtype == 0 ? pick_rank<N, RW, KIND, FacF32, false>(rank, longer)
+                       : pick_rank<N, RW, KIND, FacBF16, false>(rank, longer);
 }
 
 // (record words, layout kind) pairs the planner can choose for N modes
 template <int N>
-EcFn pick_layout(int rank, int fdtype, int words, int kind, EcForm form) {
+EcFn pick_layout(int rank, int fdtype, int words, int kind, EcForm form, bool longer) {
     if constexpr (N <= 2) {
-        if (words == 3 && kind == kWord32) return pick_rank<N, 3, kWord32>(rank, fdtype, form);
-        if (words == 4 && kind == kWord32) return pick_rank<N, 4, kWord32>(rank, fdtype, form);
+        if (words == 3 && kind == kWord32) return pick_form<N, 3, kWord32>(rank, fdtype, form, longer);
+        if (words == 4 && kind == kWord32) return pick_form<N, 4, kWord32>(rank, fdtype, form, longer);
     } else if constexpr (N == 3) {
-        if (words == 3 && kind == kPacked) return pick_rank<N, 3, kPacked>(rank, fdtype, form);
-        if (words == 4 && kind == kWord32) return pick_rank<N, 4, kWord32>(rank, fdtype, form);
+        if (words == 3 && kind == kPacked) return pick_form<N, 3, kPacked>(rank, fdtype, form, longer);
+        if (words == 4 && kind == kWord32) return pick_form<N, 4, kWord32>(rank, fdtype, form, longer);
     } else if constexpr (N <= 6) {
         if constexpr (N == 4)
-            if (words == 3 && kind == kHalf16) return pick_rank<N, 3, kHalf16>(rank, fdtype, form);
-        if (words == 3 && kind == kPacked) return pick_rank<N, 3, kPacked>(rank, fdtype, form);
-        if (words == 4 && kind == kHalf16) return pick_rank<N, 4, kHalf16>(rank, fdtype, form);
-        if (words == 4 && kind == kPacked) return pick_rank<N, 4, kPacked>(rank, fdtype, form);
-        if (words == 8 && kind == kWord32) return pick_rank<N, 8, kWord32>(rank, fdtype, form);
+            if (words == 3 && kind == kHalf16) return pick_form<N, 3, kHalf16>(rank, fdtype, form, longer);
+        if (words == 3 && kind == kPacked) return pick_form<N, 3, kPacked>(rank, fdtype, form, longer);
+        if (words == 4 && kind == kHalf16) return pick_form<N, 4, kHalf16>(rank, fdtype, form, longer);
+        if (words == 4 && kind == kPacked) return pick_form<N, 4, kPacked>(rank, fdtype, form, longer);
+        if (words == 8 && kind == kWord32) return pick_form<N, 8, kWord32>(rank, fdtype, form, longer);
     } else if constexpr (N == 7) {
-        if (words == 3 && kind == kPacked) return pick_rank<N, 3, kPacked>(rank, fdtype, form);
-        if (words == 8 && kind == kWord32) return pick_rank<N, 8, kWord32>(rank, fdtype, form);
+        if (words == 3 && kind == kPacked) return pick_form<N, 3, kPacked>(rank, fdtype, form, longer);
+        if (words == 8 && kind == kWord32) return pick_form<N, 8, kWord32>(rank, fdtype, form, longer);
     } else {
-        if (words == 3 && kind == kPacked) return pick_rank<N, 3, kPacked>(rank, fdtype, form);
-        if (words == 8 && kind == kHalf16) return pick_rank<N, 8, kHalf16>(rank, fdtype, form);
-        if (words == 12 && kind == kWord32) return pick_rank<N, 12, kWord32>(rank, fdtype, form);
+        if (words == 3 && kind == kPacked) return pick_form<N, 3, kPacked>(rank, fdtype, form, longer);
+        if (words == 8 && kind == kHalf16) return pick_form<N, 8, kHalf16>(rank, fdtype, form, longer);
+        if (words == 12 && kind == kWord32) return pick_form<N, 12, kWord32>(rank, fdtype, form, longer);
     }
     return nullptr;
 }

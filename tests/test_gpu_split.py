@@ -41,6 +41,12 @@ SHAPES = [
     ("kappa8192", _zipf((300, 200, 40_000), 100_000), 32, 8192),
     ("four_modes", _zipf((300, 200, 400, 30), 60_000), 64, 300),
     ("two_modes", _zipf((3000, 200), 60_000), 8, 300),
+    ("eight_modes_r8", _zipf((9, 8, 7, 6, 5, 4, 3, 2), 6_000), 8, 3),
+    # partitions of 4095 and 4096 nonzeros (longer steps at R 16, and at R 32 with BF16)
+    ("steps_4095", _zipf((300, 200, 400, 30), 5 * 4095), 16, 5),
+    ("steps_4096", _zipf((300, 200, 400, 30), 5 * 4096), 16, 5),
+    ("steps_4096_r32", _zipf((300, 200, 400, 30), 300 * 4096), 32, 300),
+    ("longer_eight_modes", _zipf((9, 8, 7, 6, 5, 4, 3, 2), 20_000), 16, 2),
 ]
 
 
