@@ -146,7 +146,9 @@ struct EcChoice {
 //   pays on large skewed tensors (8e7, R 32: 982-1007 / 905-955; 2e7, repeats
 //   0.23-0.66: 240-246 / 226-233), not where most rows differ (8e7, repeats
 //   0.04-0.20: 1532-2053 / 1564-2106) and not on small tensors, whose rows
-//   hit the caches anyway (5e6, repeats 0.51-0.57: 57-61 / 60-66).
+//   hit the caches anyway (5e6, R 32, repeats 0.51-0.57: 57-61 / 60-66; 3e5,
+//   R 64, 147 partitions: 20-24 / 22-26), unless the rows are long (4e6, R 128,
+//   repeats 0.52-0.55: 149-157 / 137-141; 4e6, R 64: 79-80 / 74-75).
 // - Waves per partition: up to 256 partitions leave CUs idle or with one
 //   workgroup, so the most waves (1e5 nonzeros, 49 partitions, R 16: 39 us at 1,
 //   17 at 4, 14 at 8; 3e5, 147 partitions, R 64: 80 / 32 / 21).  Above that 4:
@@ -187,7 +189,8 @@ EcChoice choose_ec(int nmodes, int rank, int fdtype, int words, int kind, int ka
 #ifdef SPT_EC_FORM  // build option: 0 = always the plain form, 1 = always the reuse form
     const bool want = SPT_EC_FORM != 0;
 #else
-    const bool pays = (nmodes >= 4 && !(one_wave && kappa < 4096)) || (a.repeats >= 0.4f && kappa >= 4096);
+    const bool long_rows = rank * (fdtype == 0 ? 4 : 2) >= 256 && kappa > 256 && !one_wave;
+    const bool pays = (nmodes >= 4 && !(one_wave && kappa < 4096)) || (a.repeats >= 0.4f && (kappa >= 4096 || long_rows));
     const bool want = pays && reuse_fits(c.f, reuse, ec_lds_bytes(nmodes, rank, fdtype, 1, longer));
 #endif
     if (want) c.f = reuse;
