@@ -42,6 +42,17 @@ __device__ __forceinline__ void gather_rows(const Rec<RW>& r, const ForwardArgs&
      ...);
 }
 
+// A lane's share of the model value: the sum over its 4 ranks of p (the product
+// of all modes but the last) times the last mode's row.  Which products are
+// rounded by themselves and which are fused into a sum is written out, so that
+// the residuals' last bits, and with them the FP64 loss, do not follow the
+// compiler's choice (which differs between forms of the loop around it).
+__device__ __forceinline__ float lane_sum(const float (&p)[4], const float4& last) {
+#pragma clang fp contract(off)
+    const float p1 = p[1] * last.y, p3 = p[3] * last.w;
+    return fmaf(p[0], last.x, p1) + fmaf(p[2], last.z, p3);
+}
+
 // One nonzero per group of L = R/4 lanes; the group's partial dot products
 // are summed across its lanes with butterfly shuffles.  What bounds it is the
 // latency of the gathers (the largest rows come from L2 or beyond), so a group
@@ -79,13 +90,13 @@ __global__ __launch_bounds__(256) void forward_kernel(const ForwardArgs a) {
         for (int u = 0; u < U; ++u) {
             float prod[4] = {y[u][0].x, y[u][0].y, y[u][0].z, y[u][0].w};
 #pragma unroll
-            for (int w = 1; w < N; ++w) {
+            for (int w = 1; w < N - 1; ++w) {
                 prod[0] *= y[u][w].x;
                 prod[1] *= y[u][w].y;
                 prod[2] *= y[u][w].z;
                 prod[3] *= y[u][w].w;
             }
-            float m = (prod[0] + prod[1]) + (prod[2] + prod[3]);
+            float m = lane_sum(prod, y[u][N - 1]);
 #pragma unroll
             for (int off = 1; off < L; off <<= 1) m += __shfl_xor(m, off, L);
             if (li == 0 && p + u * stride < a.nnz) {
