@@ -93,13 +93,11 @@ __global__ __launch_bounds__(kStageThreads) void stage_tables_kernel(const int32
 // One level of the merge of a chunk's sorted runs: runs of 2^rshift entries
 // pair up (2^rshift < chunk); an entry's place in the pair is its place in its
 // own run plus the number of smaller destinations in the other (one binary
-// search; destinations are distinct).  Offsets become offsets inside the
-// pair.  LAST (the pair is the chunk): the offset's bits above 16 go into the
-// destination word.  What bounds it is the searches' reads, rshift + 1 per
-// entry and level: five levels from 4096 to 131072 take 70 per entry where one
-// search in each of the chunk's 31 other runs took 372 (1e7 records: 0.61 against
-// 1.78 ms on the MI355X).
-template <bool LAST>
+// search; destinations are distinct).  Offsets become offsets inside the pair,
+// their bits above 16 kept above the destination at every level.  What bounds
+// it is the searches' reads, rshift + 1 per entry and level: five levels from
+// 4096 to 131072 take 75 per entry where one search in each of the chunk's 31
+// other runs took 372 (1e7 records: 0.61 against 1.78 ms on the MI355X).
 __global__ __launch_bounds__(kStageThreads) void merge_pairs_kernel(const int32_t* __restrict__ sdst,
                                                                     const uint16_t* __restrict__ soff, int64_t nnz,
                                                                     int rshift, int dbits, int32_t* __restrict__ ddst,
@@ -109,16 +107,17 @@ __global__ __launch_bounds__(kStageThreads) void merge_pairs_kernel(const int32_
     const int64_t run = int64_t(1) << rshift;
     const int64_t r0 = i & ~(run - 1), p0 = i & ~(2 * run - 1);
     const int64_t o0 = r0 ^ run;  // the other run of the pair
-    const int32_t key = sdst[i];
+    const uint32_t dmask = (1u << dbits) - 1u;
+    const uint32_t t = (uint32_t)sdst[i], key = t & dmask;
     int64_t lo = o0 < nnz ? o0 : nnz, hi = o0 + run < nnz ? o0 + run : nnz;
     const int64_t first = lo;
     while (lo < hi) {
         const int64_t mid = (lo + hi) >> 1;
-        if (sdst[mid] < key) lo = mid + 1; else hi = mid;
+        if (((uint32_t)sdst[mid] & dmask) < key) lo = mid + 1; else hi = mid;
     }
     const int64_t pos = p0 + (i - r0) + (lo - first);
-    const uint32_t off = (uint32_t)(r0 - p0) + soff[i];
-    ddst[pos] = LAST ? (int32_t)((uint32_t)key | ((off >> 16) << dbits)) : key;
+    const uint32_t off = (uint32_t)(r0 - p0) + ((t >> dbits) << 16 | soff[i]);
+    ddst[pos] = (int32_t)(key | ((off >> 16) << dbits));
     doff[pos] = (uint16_t)(off & 0xFFFFu);
 }
 
@@ -180,12 +179,8 @@ void launch_stage_tables(int words, const int32_t* nxt, int64_t nnz, int32_t* dd
     uint16_t *from_off = (cshift - kSubShift) % 2 ? tmp_off : doff, *to_off = (cshift - kSubShift) % 2 ? doff : tmp_off;
     hipLaunchKernelGGL(stage_tables_kernel<kSub>, dim3(subs), dim3(kStageThreads), 0, s, nxt, nnz, from_dst, from_off);
     for (int r = kSubShift; r < cshift; ++r) {
-        if (r + 1 == cshift)
-            hipLaunchKernelGGL((merge_pairs_kernel<true>), dim3(blocks), dim3(kStageThreads), 0, s,
-                               (const int32_t*)from_dst, (const uint16_t*)from_off, nnz, r, dest_bits(nnz), to_dst, to_off);
-        else
-            hipLaunchKernelGGL((merge_pairs_kernel<false>), dim3(blocks), dim3(kStageThreads), 0, s,
-                               (const int32_t*)from_dst, (const uint16_t*)from_off, nnz, r, dest_bits(nnz), to_dst, to_off);
+        hipLaunchKernelGGL(merge_pairs_kernel, dim3(blocks), dim3(kStageThreads), 0, s, (const int32_t*)from_dst,
+                           (const uint16_t*)from_off, nnz, r, dest_bits(nnz), to_dst, to_off);
         int32_t* const d = from_dst;
         from_dst = to_dst;
         to_dst = d;
