@@ -88,10 +88,9 @@ struct spt_tensor_s {
     double* ipart = nullptr;
     double* Vinv = nullptr;
     uint16_t* shadow[8] = {};  // BF16 copies of the factors (CP-ALS with SPT_BF16)
-    uint32_t* res[2] = {nullptr, nullptr};  // residual stream + its remap target
-    int res_cur = 0;                        // res[res_cur]: residuals in mode res_mode's order
-    int res_mode = 0;
-    int res_rank = 0;                       // rank of the last forward pass (0: none)
+    uint32_t* res[3] = {};  // residual stream + the streams of the other modes
+    int res_cur = 0;        // res[res_cur]: residuals in mode 0's order
+    int res_rank = 0;       // rank of the last forward pass (0: none)
     double* loss_part = nullptr;
     double* Gsum = nullptr;
     double* Isum = nullptr;
@@ -916,10 +915,19 @@ spt_status grad_args(spt_tensor_t t, const void* const* factors, spt_dtype fdtyp
     if (!t->copies && t->cur_mode != 0) return fail(SPT_ERR_STATE, "stream must be in mode 0's order");
     spt_status st = ensure_carry(t, rank);
     if (st != SPT_OK) return st;
-    if (!t->res[0]) {
-        const int nres = t->copies ? 1 : 2;
-        for (int k = 0; k < nres; ++k)
-            if ((st = dalloc(t, &t->res[k], (size_t)(t->nnz * t->lay.words), &t->allocs)) != SPT_OK) return st;
+    if (!t->loss_part) {
+        // the adjoint can do with one stream (one copy per mode) or two, at the
+        // cost of another pass; with one more, mode 0's stays where it is
+        const int need = t->copies ? 1 : 2, want = t->copies || t->N == 2 ? 2 : 3;
+        for (int k = 0; k < want; ++k) {
+            if (t->res[k]) continue;
+            st = dalloc(t, &t->res[k], (size_t)(t->nnz * t->lay.words), &t->allocs);
+            if (st != SPT_OK && k < need) return st;
+            if (st != SPT_OK) {
+                g_last_error.clear();
+                (void)hipGetLastError();
+            }
+        }
         if ((st = dalloc(t, &t->loss_part, (size_t)spt::forward_blocks(t->nnz), &t->allocs)) != SPT_OK)
             return st;
     }
@@ -936,45 +944,44 @@ spt_status run_loss(spt_tensor_t t, const void* const* factors, int32_t rank, do
     HIPCHK(hipGetLastError());
     t->res_rank = rank;
     t->res_cur = 0;
-    t->res_mode = 0;
     return SPT_OK;
 }
 
-// The adjoint of every mode from the residual stream of the last forward
-// pass (res[res_cur], in mode res_mode's order), remapped mode to mode.  The
-// modes are taken from that one on, wherever it is, so N modes need N - 1
-// remaps and the stream stays in the last mode's order (the remap back to mode
-// 0's took 0.62 of the 6.7 ms of loss and gradient at 4 modes, 5e7 nonzeros,
-// R 16).  With one copy per mode each further mode's residuals are formed from
-// that mode's own stream, and the last mode's stay.
+// The adjoint of every mode from the residual stream of the last forward pass
+// (res[res_cur], in mode 0's order), remapped mode to mode.  That stream stays
+// as it is and the other modes' are written in turn to the other two buffers,
+// so N modes need N - 1 remaps (the remap back to mode 0's order took 0.62 of
+// the 6.7 ms of loss and gradient at 4 modes, 5e7 nonzeros, R 16) and the call
+// may be repeated, also as a captured graph.  Where the third buffer was not to
+// be had, the two are written in turn and the last remap leads back.  With one
+// copy per mode the other modes' residuals are formed from their own streams.
 spt_status run_adjoint(spt_tensor_t t, const void* const* factors, int32_t rank, void* const* grads,
                        hipStream_t s) {
     const int N = t->N;
     spt_status st;
     if (t->copies) {
-        for (int k = 0; k < N; ++k) {
-            if (k > 0) {
-                const int next = (t->res_mode + 1) % N;
-                if ((st = launch_forward_pass(t, t->rec_mode[next], t->res[0], factors, rank, s)) != SPT_OK) return st;
-                t->res_mode = next;
-            }
-            if ((st = launch_mode(t, t->res_mode, t->res[0], nullptr, factors, SPT_F32, rank,
-                                  (float*)grads[t->res_mode], s)) != SPT_OK)
+        uint32_t* const other = t->res[1] ? t->res[1] : t->res[0];
+        for (int d = 0; d < N; ++d) {
+            if (d > 0 && (st = launch_forward_pass(t, t->rec_mode[d], other, factors, rank, s)) != SPT_OK) return st;
+            if ((st = launch_mode(t, d, d > 0 ? other : t->res[0], nullptr, factors, SPT_F32, rank, (float*)grads[d],
+                                  s)) != SPT_OK)
                 return st;
         }
+        if (!t->res[1]) return launch_forward_pass(t, t->rec_mode[0], t->res[0], factors, rank, s);
         return SPT_OK;
     }
-    for (int k = 0; k < N; ++k) {
-        const int d = t->res_mode;
-        const bool last = k == N - 1;
-        if ((st = launch_mode(t, d, t->res[t->res_cur], last ? nullptr : t->res[1 - t->res_cur], factors, SPT_F32,
-                              rank, (float*)grads[d], s)) != SPT_OK)
+    const bool stays = N == 2 || t->res[2];
+    uint32_t *in = t->res[t->res_cur], *out = t->res[1 - t->res_cur];
+    for (int d = 0; d < N; ++d) {
+        const bool last = d == N - 1;
+        if ((st = launch_mode(t, d, in, last && stays ? nullptr : out, factors, SPT_F32, rank, (float*)grads[d], s)) !=
+            SPT_OK)
             return st;
-        if (!last) {
-            t->res_cur = 1 - t->res_cur;
-            t->res_mode = (d + 1) % N;
-        }
+        uint32_t* const next = stays && d == 0 ? t->res[2] : in;
+        in = out;
+        out = next;
     }
+    if (!stays && N % 2) t->res_cur = 1 - t->res_cur;  // N remaps: mode 0's order again
     return SPT_OK;
 }
 

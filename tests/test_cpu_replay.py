@@ -15,6 +15,7 @@ import numpy as np
 import pytest
 
 import test_cpu_kernels as K
+from paper_2405_08470_amd import synth
 from test_cpu_kernels import T, lib  # noqa: F401 (lib: the fixture that builds the objects)
 
 WRAPPED = ["_ZN3spt9launch_ecEiiiiiiRKNS_6EcArgsEP13cpuhip_stream",
@@ -94,3 +95,84 @@ def test_residuals_have_the_written_roundings(lib, replay_lib, N, R, copies):  #
     r = want.astype(np.float64)
     assert abs(loss[0] - 0.5 * (r * r).sum()) <= 1e-14 * loss[0]
     t.free()
+
+
+SHAPES = [(60, 50), (30, 20, 40), (20, 15, 12, 6), (12, 11, 10, 9, 8)]
+
+
+def _adjoint_of(L, dims, **kw):
+    idx, val = synth.random_coo(dims, 1024, seed=7, dist="zipf", zipf_s=1.1)
+    Y = [0.5 * y for y in synth.random_factors(dims, 16, seed=18)]
+    t = T(L, dims, idx, val, kappa=5, **kw)
+    t.mttkrp(0, Y, 16, flags=0)  # the workspace of this rank
+    grads = [np.zeros_like(y) for y in Y]
+
+    def loss():
+        assert L.spt_cp_loss(t.h, ptrs(Y), 0, 16, np.zeros(1).ctypes.data, None) == 0, L.spt_last_error()
+
+    def adjoint():
+        assert L.spt_cp_adjoint(t.h, ptrs(Y), 0, 16, ptrs(grads), None) == 0, L.spt_last_error()
+
+    def taken():
+        out = [g.view(np.uint32).copy() for g in grads]
+        for g in grads:
+            g.fill(np.nan)
+        return out
+    return t, loss, adjoint, taken
+
+
+@pytest.mark.parametrize("lib", ["chosen"], indirect=True)
+@pytest.mark.parametrize("kw", [{}, {"dr": 1}, {"copies": 1}], ids=["staged", "fused", "copies"])
+@pytest.mark.parametrize("dims", SHAPES, ids=len)
+def test_recorded_adjoint_runs_again(lib, replay_lib, dims, kw):  # noqa: F811
+    L = replay_lib
+    t, loss, adjoint, taken = _adjoint_of(L, dims, **kw)
+    loss()
+    L.cpuhip_record(1)
+    adjoint()
+    L.cpuhip_record(0)
+    want = taken()
+    for _ in range(3):
+        assert L.cpuhip_replay() >= 2 * len(dims)
+        assert all(np.array_equal(a, b) for a, b in zip(taken(), want))
+    adjoint()
+    assert all(np.array_equal(a, b) for a, b in zip(taken(), want))
+    t.free()
+
+
+@pytest.mark.parametrize("lib", ["chosen"], indirect=True)
+@pytest.mark.parametrize("kw", [{}, {"dr": 1}, {"copies": 1}], ids=["staged", "fused", "copies"])
+@pytest.mark.parametrize("dims", SHAPES[1:], ids=len)
+def test_adjoint_without_the_spare_stream(lib, replay_lib, dims, kw):  # noqa: F811
+    L = replay_lib
+    t, loss, adjoint, taken = _adjoint_of(L, dims, **kw)
+    loss()
+    adjoint()
+    want, whole = taken(), t.info().device_bytes
+    t.free()
+    t, loss, adjoint, taken = _adjoint_of(L, dims, **kw)
+    L.cpuhip_fail_malloc(1 if kw.get("copies") else 2)
+    loss()
+    assert t.info().device_bytes == whole - t.nnz * t.info().record_bytes
+    for _ in range(3):
+        adjoint()
+        assert all(np.array_equal(a, b) for a, b in zip(taken(), want))
+    loss()
+    adjoint()
+    assert all(np.array_equal(a, b) for a, b in zip(taken(), want))
+    t.free()
+
+
+@pytest.mark.parametrize("lib", ["chosen"], indirect=True)
+def test_loss_is_refused_without_its_streams(lib, replay_lib):  # noqa: F811
+    """Every allocation that is needed, failed in turn: refused, and the next
+    call finds what it needs."""
+    L = replay_lib
+    for k in (0, 1, 3):
+        t, loss, adjoint, taken = _adjoint_of(L, SHAPES[1])
+        Y = [0.5 * y for y in synth.random_factors(SHAPES[1], 16, seed=18)]
+        L.cpuhip_fail_malloc(k)
+        assert L.spt_cp_loss(t.h, ptrs(Y), 0, 16, np.zeros(1).ctypes.data, None) != 0
+        loss()
+        adjoint()
+        t.free()
