@@ -73,8 +73,7 @@ struct spt_tensor_s {
     int32_t nsplit[8] = {}, nslots[8] = {}, nempty[8] = {};
     int64_t max_load[8] = {};
     float repeats[8] = {};
-    std::vector<int32_t> order0;  // input nonzero at each mode-0 position (host planner)
-    int32_t* order0_dev = nullptr;  // ... of the device planner, read by spt_tensor_get_remap only
+    std::unique_ptr<int32_t[]> remap0;  // host: mode-0 position of each input nonzero (copies == 0)
     double norm_sq = 0.0;
     double prep_seconds = 0.0;
     int64_t device_bytes = 0;
@@ -553,7 +552,7 @@ spt_status load_device(int32_t nmodes, const int64_t* dims, int64_t nnz, const i
             delete t;
             return st;
         }
-        t->order0_dev = dp.order0;
+        t->remap0 = std::move(dp.remap0);
         t->cur = 0;
         t->cur_mode = 0;
     } catch (const std::bad_alloc&) {
@@ -668,7 +667,10 @@ spt_status spt_tensor_load_coo(int32_t nmodes, const int64_t* dims, int64_t nnz,
             delete t;
             return st;
         }
-        t->order0 = plan.mode[0].order;
+        if (!copies) {
+            t->remap0.reset(new int32_t[std::max<int64_t>(1, nnz)]);
+            std::copy(plan.mode[0].remap.begin(), plan.mode[0].remap.end(), t->remap0.get());
+        }
         t->cur = 0;
         t->cur_mode = 0;
         t->dr = dr;
@@ -1042,15 +1044,9 @@ spt_status spt_tensor_get_remap(spt_tensor_t t, int32_t mode, int64_t* b_host) {
     if (t->copies) return fail(SPT_ERR_UNSUPPORTED, "no remap ids are held with one copy per mode");
     const int64_t nnz = t->nnz;
     try {
-        // b_0 from the mode-0 stream, then follow the device's next-position
+        // b_0 as the load kept it, then follow the device's next-position
         // arrays mode by mode
-        std::vector<int32_t> pos(nnz), nx(nnz);
-        const int32_t* order0 = t->order0.data();
-        if (t->order0_dev) {
-            if (nnz) HIPCHK(hipMemcpy(nx.data(), t->order0_dev, sizeof(int32_t) * nnz, hipMemcpyDeviceToHost));
-            order0 = nx.data();
-        }
-        for (int64_t p = 0; p < nnz; ++p) pos[order0[p]] = (int32_t)p;
+        std::vector<int32_t> pos(t->remap0.get(), t->remap0.get() + nnz), nx(mode > 0 ? nnz : 0);
         for (int d = 0; d < mode; ++d) {
             if (nnz) HIPCHK(hipMemcpy(nx.data(), t->nxt[d], sizeof(int32_t) * nnz, hipMemcpyDeviceToHost));
             for (int64_t e = 0; e < nnz; ++e) pos[e] = nx[pos[e]];

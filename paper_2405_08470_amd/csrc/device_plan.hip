@@ -394,6 +394,19 @@ struct Temps {
     }
 };
 
+// A second stream for the length of a call.
+struct SideStream {
+    hipStream_t stream = nullptr;
+    hipEvent_t event = nullptr;
+    // the side stream starts after what is enqueued on `s` so far
+    void fork(hipStream_t s);
+    ~SideStream() {
+        if (stream) (void)hipStreamSynchronize(stream);
+        if (stream) (void)hipStreamDestroy(stream);
+        if (event) (void)hipEventDestroy(event);
+    }
+};
+
 struct JoinAll {
     std::vector<std::thread> th;
     void join() {
@@ -406,6 +419,13 @@ struct JoinAll {
 void check(hipError_t e, const char* what) {
     if (e != hipSuccess)
         throw Fail{DevicePlanError::kHip, std::string(what) + ": " + hipGetErrorString(e)};
+}
+
+void SideStream::fork(hipStream_t s) {
+    check(hipStreamCreateWithFlags(&stream, hipStreamNonBlocking), "stream");  // default priority
+    check(hipEventCreateWithFlags(&event, hipEventDisableTiming), "event");
+    check(hipEventRecord(event, s), "event");
+    check(hipStreamWaitEvent(stream, event, 0), "event");
 }
 
 template <typename K, typename... Args>
@@ -491,6 +511,7 @@ DevicePlanError build_plan_device(int N, const int64_t* dims, int64_t nnz, const
 
         Temps tmp;
         tmp.stream = s;
+        SideStream side;  // (ends before the buffers it reads)
         int64_t maxI = 1;
         for (int w = 0; w < N; ++w) maxI = std::max<int64_t>(maxI, dims[w]);
         // indices, values, sort buffers (4), per mode: row-sorted keys and
@@ -546,6 +567,13 @@ DevicePlanError build_plan_device(int N, const int64_t* dims, int64_t nnz, const
         std::vector<RowPieces> pieces(N);
         std::vector<std::vector<int64_t>> deg(N);
         JoinAll lpt;
+        if (!copies) {
+            // host memory of mode 0's remap ids, its pages touched meanwhile
+            out->remap0.reset(new int32_t[std::max<int64_t>(1, nnz)]);
+            lpt.th.emplace_back([p = out->remap0.get(), nnz] {
+                for (int64_t i = 0; i < nnz; i += 1024) p[i] = 0;
+            });
+        }
         for (int w = 0; w < N; ++w) {
             rowK[w] = tmp.alloc<uint32_t>(nnz);
             rowE[w] = tmp.alloc<int32_t>(nnz);
@@ -599,6 +627,8 @@ DevicePlanError build_plan_device(int N, const int64_t* dims, int64_t nnz, const
             pa.bits[w] = lay.bits[w];
         }
         std::vector<int32_t*> remap(N);
+        hipError_t copied = hipSuccess;
+        JoinAll copier;  // (ends before what it reads and writes)
         for (int w = 0; w < N; ++w) remap[w] = tmp.alloc<int32_t>(nnz);
         if (nnz > 0) launch(iota_kernel, g, kT, s, sb.v[0], nnz);
         auto sort_by = [&](int w) {
@@ -617,9 +647,21 @@ DevicePlanError build_plan_device(int N, const int64_t* dims, int64_t nnz, const
                        same + d * kRunWindows);
             if (nnz > 0) launch(scatter_pos_kernel, g, kT, s, (const int32_t*)sb.v[0], nnz, remap[d]);
             if (d == 0 && !copies) {
-                out->order0 = static_cast<int32_t*>(palloc(sizeof(int32_t) * nnz));
-                if (nnz > 0)
-                    check(hipMemcpyAsync(out->order0, sb.v[0], sizeof(int32_t) * nnz, hipMemcpyDeviceToDevice, s), "copy");
+                // mode 0's remap ids come to the host (spt_tensor_get_remap reads
+                // them) beside the rest of the work: a copy to pageable memory
+                // holds the thread that asks for it, so another one does
+                if (nnz > 0) {
+                    side.fork(s);
+                    int dev = 0;
+                    check(hipGetDevice(&dev), "device");
+                    copier.th.emplace_back([&, dev] {
+                        copied = hipSetDevice(dev);
+                        if (copied == hipSuccess)
+                            copied = hipMemcpyAsync(out->remap0.get(), remap[0], sizeof(int32_t) * nnz,
+                                                    hipMemcpyDeviceToHost, side.stream);
+                        if (copied == hipSuccess) copied = hipStreamSynchronize(side.stream);
+                    });
+                }
             }
             if (copies || d == 0) {
                 uint32_t* r = static_cast<uint32_t*>(palloc(sizeof(uint32_t) * lay.words * nnz));
@@ -678,6 +720,8 @@ DevicePlanError build_plan_device(int N, const int64_t* dims, int64_t nnz, const
             check(hipMemcpyAsync(hsame.data(), same, sizeof(int32_t) * hsame.size(), hipMemcpyDeviceToHost, s),
                   "download");
         check(hipStreamSynchronize(s), "device planner");
+        copier.join();
+        check(copied, "download remap ids");
         int64_t seen = 0;
         for (int w = 0; w < kRunWindows; ++w)
             seen += std::max<int64_t>(0, std::min<int64_t>(nnz, run_window_start(w, nnz) + kRunWindow) -

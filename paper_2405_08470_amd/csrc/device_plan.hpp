@@ -12,6 +12,7 @@
 
 #include <cstdint>
 #include <functional>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -26,7 +27,7 @@ struct DevicePlan {
     uint32_t* rec0 = nullptr;                 // stream in mode 0's order (copies == 0)
     int32_t* nxt[kMaxModes] = {};             // next positions (copies == 0)
     uint32_t* rec_mode[kMaxModes] = {};       // one stream per mode (copies == 1)
-    int32_t* order0 = nullptr;                // input nonzero at each mode-0 position (copies == 0)
+    std::unique_ptr<int32_t[]> remap0;        // host: mode-0 position of each input nonzero (copies == 0)
     double norm_sq = 0.0;
 };
 
