@@ -423,6 +423,7 @@ spt_status spt_plan_coo(int32_t nmodes, const int64_t* dims, int64_t nnz, const 
     if (!msg.empty()) return fail(range ? SPT_ERR_OUT_OF_RANGE : SPT_ERR_INVALID_ARG, msg);
     po.remap_ids = remap != nullptr;
     po.norm = false;
+    po.repeats = false;
     if (!part && !remap && !ptr) {
         if (kappa_out) *kappa_out = po.kappa > 0 ? po.kappa : spt::default_kappa(nnz);
         return SPT_OK;

@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <cstring>
 #include <functional>
+#include <numeric>
 #include <queue>
 #include <thread>
 #include <utility>
@@ -473,17 +474,24 @@ void build_plan(int nmodes, const int64_t* dims, int64_t nnz, const int32_t* idx
             ModePlan& mp = plan->mode[d];
             mp.order = order;
             const int32_t *rows = idx + (int64_t)d * nnz, *last = idx + (int64_t)((d + N - 1) % N) * nnz;
-            int64_t seen = 0, same = 0;
-            for (int w = 0; w < kRunWindows; ++w) {
-                const int64_t p0 = run_window_start(w, nnz), p1 = std::min<int64_t>(nnz, p0 + kRunWindow);
-                for (int64_t p = p0 + 1; p < p1; ++p, ++seen)
-                    same += rows[order[p]] == rows[order[p - 1]] && last[order[p]] == last[order[p - 1]];
-            }
-            mp.repeats = seen ? (double)same / (double)seen : 0.0;
+            std::vector<int64_t> seen(num_threads(), 0), same(num_threads(), 0);
             mp.remap.resize(nnz);
-            parallel_for(nnz, num_threads(), [&](int64_t b, int64_t e, int) {
+            parallel_for(nnz, num_threads(), [&](int64_t b, int64_t e, int t) {
                 for (int64_t p = b; p < e; ++p) mp.remap[order[p]] = (int32_t)p;
+                if (!opt.repeats) return;
+                // the windows that start in this span
+                int64_t hits = 0, steps = 0;
+                for (int w = 0; w < kRunWindows; ++w) {
+                    const int64_t p0 = run_window_start(w, nnz), p1 = std::min<int64_t>(nnz, p0 + kRunWindow);
+                    if (p0 < b || p0 >= e) continue;
+                    for (int64_t p = p0 + 1; p < p1; ++p, ++steps)
+                        hits += rows[order[p]] == rows[order[p - 1]] && last[order[p]] == last[order[p - 1]];
+                }
+                seen[t] = steps;
+                same[t] = hits;
             });
+            const int64_t all = std::accumulate(seen.begin(), seen.end(), int64_t(0));
+            mp.repeats = all ? (double)std::accumulate(same.begin(), same.end(), int64_t(0)) / (double)all : 0.0;
         }
     }
     seg.clear();
