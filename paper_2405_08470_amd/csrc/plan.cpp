@@ -100,7 +100,11 @@ void counting_sort(const int32_t* in, int64_t n, const int32_t* key, int64_t nke
 // binary searches for the segments.
 void least_filled(const std::vector<uint32_t>& order, const std::vector<int32_t>& size, int64_t max_size,
                   int32_t kappa, std::vector<int32_t>& part, std::vector<int64_t>& loads) {
-    if (max_size > (1 << 20)) {  // few, very heavy items: a heap on (load, id)
+    // few, heavy items: a heap on (load, id), as the ring's empty lists alone would
+    // cost more (a heaviest item of 1e6 nonzeros, one core: 250 rows 0.02 ms by the
+    // heap, 3-4 by the ring, 4000 rows 0.5-0.8 and 3.6-5.2; of 65000, where the
+    // ring is taken: 0.2-0.3 by either and 0.4-1.2)
+    if (max_size > 16 * (int64_t)order.size() + 65536) {
         using LoadId = std::pair<int64_t, int32_t>;
         std::priority_queue<LoadId, std::vector<LoadId>, std::greater<LoadId>> heap;
         for (int32_t z = 0; z < kappa; ++z) heap.push(LoadId(0, z));
