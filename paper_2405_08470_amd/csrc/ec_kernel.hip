@@ -148,7 +148,9 @@ struct EcChoice {
 //   0.04-0.20: 1532-2053 / 1564-2106) and not on small tensors, whose rows
 //   hit the caches anyway (5e6, R 32, repeats 0.51-0.57: 57-61 / 60-66; 3e5,
 //   R 64, 147 partitions: 20-24 / 22-26), unless the rows are long (4e6, R 128,
-//   repeats 0.52-0.55: 149-157 / 137-141; 4e6, R 64: 79-80 / 74-75).
+//   repeats 0.52-0.55: 149-157 / 137-141; 4e6, R 64: 79-80 / 74-75).  With N = 2 the kept row is the
+//   only one, and every nonzero waits for the branch (1e7, R 32, repeats 0.45:
+//   89 / 113; R 64: 147 / 235; 3e7, R 64: 376 / 575).
 // - Waves per partition: up to 256 partitions leave CUs idle or with one
 //   workgroup, so the most waves (1e5 nonzeros, 49 partitions, R 16: 39 us at 1,
 //   17 at 4, 14 at 8; 3e5, 147 partitions, R 64: 80 / 32 / 21).  Above that 4:
@@ -190,7 +192,7 @@ EcChoice choose_ec(int nmodes, int rank, int fdtype, int words, int kind, int ka
     const bool want = SPT_EC_FORM != 0;
 #else
     const bool long_rows = rank * (fdtype == 0 ? 4 : 2) >= 256 && kappa > 256 && !one_wave;
-    const bool pays = (nmodes >= 4 && !(one_wave && kappa < 4096)) || (a.repeats >= 0.4f && (kappa >= 4096 || long_rows));
+    const bool pays = (nmodes >= 4 && !(one_wave && kappa < 4096)) || (nmodes == 3 && a.repeats >= 0.4f && (kappa >= 4096 || long_rows));
     const bool want = pays && reuse_fits(c.f, reuse, ec_lds_bytes(nmodes, rank, fdtype, 1, longer));
 #endif
     if (want) c.f = reuse;
