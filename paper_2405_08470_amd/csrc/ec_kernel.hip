@@ -11,13 +11,13 @@
 
 namespace spt {
 
-EcFnPtr pick_ec_n2(int, int, int, int, EcForm, bool);
-EcFnPtr pick_ec_n3(int, int, int, int, EcForm, bool);
-EcFnPtr pick_ec_n4(int, int, int, int, EcForm, bool);
-EcFnPtr pick_ec_n5(int, int, int, int, EcForm, bool);
-EcFnPtr pick_ec_n6(int, int, int, int, EcForm, bool);
-EcFnPtr pick_ec_n7(int, int, int, int, EcForm, bool);
-EcFnPtr pick_ec_n8(int, int, int, int, EcForm, bool);
+EcFnPtr pick_ec_n2(int, int, int, int, EcForm, int);
+EcFnPtr pick_ec_n3(int, int, int, int, EcForm, int);
+EcFnPtr pick_ec_n4(int, int, int, int, EcForm, int);
+EcFnPtr pick_ec_n5(int, int, int, int, EcForm, int);
+EcFnPtr pick_ec_n6(int, int, int, int, EcForm, int);
+EcFnPtr pick_ec_n7(int, int, int, int, EcForm, int);
+EcFnPtr pick_ec_n8(int, int, int, int, EcForm, int);
 
 namespace {
 
@@ -95,15 +95,15 @@ __global__ void remap_kernel(const uint32_t* __restrict__ in, uint32_t* __restri
     }
 }
 
-EcFnPtr pick_ec(int nmodes, int rank, int fdtype, int words, int kind, EcForm form, bool longer = false) {
+EcFnPtr pick_ec(int nmodes, int rank, int fdtype, int words, int kind, EcForm form, int steps = 1) {
     switch (nmodes) {
-        case 2: return pick_ec_n2(rank, fdtype, words, kind, form, longer);
-        case 3: return pick_ec_n3(rank, fdtype, words, kind, form, longer);
-        case 4: return pick_ec_n4(rank, fdtype, words, kind, form, longer);
-        case 5: return pick_ec_n5(rank, fdtype, words, kind, form, longer);
-        case 6: return pick_ec_n6(rank, fdtype, words, kind, form, longer);
-        case 7: return pick_ec_n7(rank, fdtype, words, kind, form, longer);
-        case 8: return pick_ec_n8(rank, fdtype, words, kind, form, longer);
+        case 2: return pick_ec_n2(rank, fdtype, words, kind, form, steps);
+        case 3: return pick_ec_n3(rank, fdtype, words, kind, form, steps);
+        case 4: return pick_ec_n4(rank, fdtype, words, kind, form, steps);
+        case 5: return pick_ec_n5(rank, fdtype, words, kind, form, steps);
+        case 6: return pick_ec_n6(rank, fdtype, words, kind, form, steps);
+        case 7: return pick_ec_n7(rank, fdtype, words, kind, form, steps);
+        case 8: return pick_ec_n8(rank, fdtype, words, kind, form, steps);
         default: return nullptr;
     }
 }
@@ -131,18 +131,20 @@ bool reuse_fits(EcFnPtr plain, EcFnPtr reuse, size_t lds) {
     return fits[{dev, plain}] = occ_reuse > 0 && occ_reuse >= std::min(occ_plain, 16);
 }
 
-// The form of the elementwise kernel and its waves per partition.
+// The form of the elementwise kernel, its waves per partition and the records
+// its lanes stage per step.
 struct EcChoice {
     EcFnPtr f;
     int waves;
-    bool longer;  // steps of more records
+    int steps;
 };
 
 // Where the lines lie (MI355X, us per launch, plain / reuse form unless said):
 // - The reuse form saves a share `repeats` of one of the N-1 gathers and pays
-//   with a branch per nonzero.  With N >= 4 that pays at every share measured:
-//   4-mode 1e7, R 16, repeats 0.15-0.71: 136-152 / 122-145; 4-mode 1e8, R 64:
-//   2692-2861 / 2282-2487; 5-mode 5e7, R 32: 860-901 / 721-802.  With N = 3 it
+//   with a branch per nonzero.  With N >= 4 that pays at every
+//   share measured (4-mode 1e7, R 16, repeats 0.15-0.71: 136-152 / 122-145;
+//   4-mode 1e8, R 64: 2692-2861 / 2282-2487; 5-mode 5e7, R 32: 860-901 /
+//   721-802).  With N = 3 it
 //   pays on large skewed tensors (8e7, R 32: 982-1007 / 905-955; 2e7, repeats
 //   0.23-0.66: 240-246 / 226-233), not where most rows differ (8e7, repeats
 //   0.04-0.20: 1532-2053 / 1564-2106) and not on small tensors, whose rows
@@ -171,10 +173,6 @@ struct EcChoice {
 //   31 / 26; two above: four gain nothing more at 977 and lose at 1710, 74).
 
 EcChoice choose_ec(int nmodes, int rank, int fdtype, int words, int kind, int kappa, const EcArgs& a) {
-    const bool longer = a.nnz / kappa >= 4096;
-    EcChoice c{pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kPlain, longer), 1, longer};
-    const EcFnPtr reuse = pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kReuse, longer);
-    if (!c.f || !reuse) return {nullptr, 1, false};
 #ifdef SPT_EC_ONE_WAVE  // build option: the order of one wave for every caller
     const bool one_wave = true;
 #else
@@ -187,19 +185,37 @@ EcChoice choose_ec(int nmodes, int rank, int fdtype, int words, int kind, int ka
 #endif
     if (one_wave && !a.rec_out && kappa < kOrderedBelow)
         if (const EcFnPtr ordered = pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kOrdered))
-            return {ordered, kappa <= 256 ? 8 : 2, false};
+            return {ordered, kappa <= 256 ? 8 : 2, 1};
+    const int64_t per = a.nnz / kappa;
+    const int lanes = ec_lanes(rank, fdtype != 0);
+    const int steps = ec_step_records(rank, fdtype != 0, per);
+    EcChoice c{pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kPlain, steps), 1, steps};
+    if (!c.f) return c;
+    if (!one_wave) c.waves = kappa <= 256 ? 8 : 4;
 #ifdef SPT_EC_FORM  // build option: 0 = always the plain form, 1 = always the reuse form
     const bool want = SPT_EC_FORM != 0;
 #else
-    const bool long_rows = rank * (fdtype == 0 ? 4 : 2) >= 256 && kappa > 256 && !one_wave;
-    const bool pays = (nmodes >= 4 && !(one_wave && kappa < 4096)) || (nmodes == 3 && a.repeats >= 0.4f && (kappa >= 4096 || long_rows));
-    const bool want = pays && reuse_fits(c.f, reuse, ec_lds_bytes(nmodes, rank, fdtype, 1, longer));
+    const bool long_rows = 16 * lanes >= 256 && kappa > 256;
+    bool want = false;
+    if (lanes == 4 && steps == 1)
+        want = false;  // (that step has no reuse form)
+    else if (nmodes >= 4)
+        want = !one_wave || kappa >= 4096;
+    else if (nmodes == 3 && a.repeats >= 0.4f)
+        want = kappa >= 4096 || (long_rows && !one_wave);
+    if (want) {
+        const EcFnPtr reuse = pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kReuse, steps);
+        want = reuse && reuse_fits(c.f, reuse, ec_lds_bytes(nmodes, rank, fdtype, 1, steps));
+    }
 #endif
-    if (want) c.f = reuse;
+    if (want) {
+        if (lanes == 4) c.steps = std::max(2, steps);
+        c.f = pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kReuse, c.steps);
+    } else if (kappa >= 8192) {
+        c.waves = 1;
+    }
 #ifdef SPT_EC_WAVES  // build option: waves per partition
     c.waves = SPT_EC_WAVES;
-#else
-    c.waves = one_wave ? 1 : kappa <= 256 ? 8 : (!want && kappa >= 8192) ? 1 : 4;
 #endif
     return c;
 }
@@ -217,11 +233,12 @@ bool launch_ec(int nmodes, int rank, int fdtype, int words, int kind, int kappa,
     if (!c.f) return false;
     EcArgs args = a;
     args.waves = c.waves;
-    // LDS of one workgroup stays within 64 KB (8 modes at rank 8 with BF16
-    // factors need 68 KB for 8 waves)
-    while (args.waves > 2 && ec_lds_bytes(nmodes, rank, fdtype, args.waves, c.longer) > 65536) args.waves /= 2;
+    // LDS of one workgroup stays within 64 KB: 4 waves where 8 would need more
+    // (70 to 121 KB: steps of 4 records from 4 modes on, with BF16 factors at any
+    // number of modes, and there steps of 2 from 5 on; 8 modes at rank 8, BF16)
+    while (args.waves > 2 && ec_lds_bytes(nmodes, rank, fdtype, args.waves, c.steps) > 65536) args.waves /= 2;
     hipLaunchKernelGGL(c.f, dim3((unsigned)kappa), dim3((unsigned)(64 * args.waves)),
-                       (size_t)ec_lds_bytes(nmodes, rank, fdtype, args.waves, c.longer), s, args);
+                       (size_t)ec_lds_bytes(nmodes, rank, fdtype, args.waves, c.steps), s, args);
     return true;
 }
 

@@ -186,15 +186,14 @@ struct EcShape {
     static constexpr int SW = N + 2;     // staged words per nonzero: indices in mode order, value, carry slot
 };
 
-template <int N, int R, int RW, int KIND, typename FT, bool REUSE, bool LONGER>
+template <int N, int R, int RW, int KIND, typename FT, bool REUSE, int K>
 __global__ __launch_bounds__(64 * kEcMaxWaves) void ec_kernel(const EcArgs a) {
     using Sh = EcShape<N, R, FT>;
     constexpr int V = Sh::V;
     constexpr int L = Sh::L;
     constexpr int G = Sh::G;
     constexpr int NG = N - 1;    // gathered factor rows per nonzero
-    constexpr int K = ec_step_records(R, FT::kBytes == 2, LONGER);  // records a lane stages per step
-    constexpr int J = K * L;     // nonzeros per group and step
+    constexpr int J = K * L;     // nonzeros per group and step: a lane stages K records
     // nonzeros whose gathers are issued together: the largest power-of-two
     // part of J with at most SPT_GATHER_INFLIGHT float4 gathers in flight per lane
     constexpr int BMAX = (SPT_GATHER_INFLIGHT / NG) > 0 ? SPT_GATHER_INFLIGHT / NG : 1;
@@ -657,22 +656,28 @@ __global__ __launch_bounds__(64 * kEcMaxWaves) void ec_ordered_kernel(const EcAr
 
 using EcFn = EcFnPtr;
 
-// (longer steps exist where a nonzero has 4 lanes)
+// (where a nonzero has 4 lanes a step takes 2 or 4 records, in the plain form
+// also 1; else 1)
 template <int N, int R, int RW, int KIND, typename FT, bool REUSE>
-EcFn pick_steps(bool longer) {
-    if constexpr (ec_step_records(R, FT::kBytes == 2, true) != ec_step_records(R, FT::kBytes == 2, false))
-        if (longer) return ec_kernel<N, R, RW, KIND, FT, REUSE, true>;
-    return ec_kernel<N, R, RW, KIND, FT, REUSE, false>;
+EcFn pick_steps(int steps) {
+    if constexpr (ec_lanes(R, FT::kBytes == 2) != 4) {
+        return ec_kernel<N, R, RW, KIND, FT, REUSE, 1>;
+    } else {
+        if (steps == 4) return ec_kernel<N, R, RW, KIND, FT, REUSE, 4>;
+        if constexpr (!REUSE)
+            if (steps == 1) return ec_kernel<N, R, RW, KIND, FT, REUSE, 1>;
+        return ec_kernel<N, R, RW, KIND, FT, REUSE, 2>;
+    }
 }
 
 template <int N, int RW, int KIND, typename FT, bool REUSE>
-EcFn pick_rank(int rank, bool longer) {
+EcFn pick_rank(int rank, int steps) {
     switch (rank) {
-        case 8: return pick_steps<N, 8, RW, KIND, FT, REUSE>(longer);
-        case 16: return pick_steps<N, 16, RW, KIND, FT, REUSE>(longer);
-        case 32: return pick_steps<N, 32, RW, KIND, FT, REUSE>(longer);
-        case 64: return pick_steps<N, 64, RW, KIND, FT, REUSE>(longer);
-        case 128: return pick_steps<N, 128, RW, KIND, FT, REUSE>(longer);
+        case 8: return pick_steps<N, 8, RW, KIND, FT, REUSE>(steps);
+        case 16: return pick_steps<N, 16, RW, KIND, FT, REUSE>(steps);
+        case 32: return pick_steps<N, 32, RW, KIND, FT, REUSE>(steps);
+        case 64: return pick_steps<N, 64, RW, KIND, FT, REUSE>(steps);
+        case 128: return pick_steps<N, 128, RW, KIND, FT, REUSE>(steps);
         default: return nullptr;
     }
 }
@@ -689,7 +694,7 @@ EcFn pick_ordered(int rank, int fdtype) {
 }
 
 template <int N, int RW, int KIND>
-EcFn pick_form(int rank, int fdtype, EcForm form, bool longer) {
+EcFn pick_form(int rank, int fdtype, EcForm form, int steps) {
     if (form == EcForm::kOrdered) {  // for the 12-byte records the library chooses by itself
         if constexpr (RW == 3)
             return pick_ordered<N, RW, KIND>(rank, fdtype);
@@ -697,35 +702,35 @@ EcFn pick_form(int rank, int fdtype, EcForm form, bool longer) {
             return nullptr;
     }
     if (form == EcForm::kReuse)
-        return fdtype == 0 ? pick_rank<N, RW, KIND, FacF32, true>(rank, longer)
-                           : pick_rank<N, RW, KIND, FacBF16, true>(rank, longer);
-    return fdtype == 0 ? pick_rank<N, RW, KIND, FacF32, false>(rank, longer)
-                       : pick_rank<N, RW, KIND, FacBF16, false>(rank, longer);
+        return fdtype == 0 ? pick_rank<N, RW, KIND, FacF32, true>(rank, steps)
+                           : pick_rank<N, RW, KIND, FacBF16, true>(rank, steps);
+    return fdtype == 0 ? pick_rank<N, RW, KIND, FacF32, false>(rank, steps)
+                       : pick_rank<N, RW, KIND, FacBF16, false>(rank, steps);
 }
 
 // (record words, layout kind) pairs the planner can choose for N modes
 template <int N>
-EcFn pick_layout(int rank, int fdtype, int words, int kind, EcForm form, bool longer) {
+EcFn pick_layout(int rank, int fdtype, int words, int kind, EcForm form, int steps) {
     if constexpr (N <= 2) {
-        if (words == 3 && kind == kWord32) return pick_form<N, 3, kWord32>(rank, fdtype, form, longer);
-        if (words == 4 && kind == kWord32) return pick_form<N, 4, kWord32>(rank, fdtype, form, longer);
+        if (words == 3 && kind == kWord32) return pick_form<N, 3, kWord32>(rank, fdtype, form, steps);
+        if (words == 4 && kind == kWord32) return pick_form<N, 4, kWord32>(rank, fdtype, form, steps);
     } else if constexpr (N == 3) {
-        if (words == 3 && kind == kPacked) return pick_form<N, 3, kPacked>(rank, fdtype, form, longer);
-        if (words == 4 && kind == kWord32) return pick_form<N, 4, kWord32>(rank, fdtype, form, longer);
+        if (words == 3 && kind == kPacked) return pick_form<N, 3, kPacked>(rank, fdtype, form, steps);
+        if (words == 4 && kind == kWord32) return pick_form<N, 4, kWord32>(rank, fdtype, form, steps);
     } else if constexpr (N <= 6) {
         if constexpr (N == 4)
-            if (words == 3 && kind == kHalf16) return pick_form<N, 3, kHalf16>(rank, fdtype, form, longer);
-        if (words == 3 && kind == kPacked) return pick_form<N, 3, kPacked>(rank, fdtype, form, longer);
-        if (words == 4 && kind == kHalf16) return pick_form<N, 4, kHalf16>(rank, fdtype, form, longer);
-        if (words == 4 && kind == kPacked) return pick_form<N, 4, kPacked>(rank, fdtype, form, longer);
-        if (words == 8 && kind == kWord32) return pick_form<N, 8, kWord32>(rank, fdtype, form, longer);
+            if (words == 3 && kind == kHalf16) return pick_form<N, 3, kHalf16>(rank, fdtype, form, steps);
+        if (words == 3 && kind == kPacked) return pick_form<N, 3, kPacked>(rank, fdtype, form, steps);
+        if (words == 4 && kind == kHalf16) return pick_form<N, 4, kHalf16>(rank, fdtype, form, steps);
+        if (words == 4 && kind == kPacked) return pick_form<N, 4, kPacked>(rank, fdtype, form, steps);
+        if (words == 8 && kind == kWord32) return pick_form<N, 8, kWord32>(rank, fdtype, form, steps);
     } else if constexpr (N == 7) {
-        if (words == 3 && kind == kPacked) return pick_form<N, 3, kPacked>(rank, fdtype, form, longer);
-        if (words == 8 && kind == kWord32) return pick_form<N, 8, kWord32>(rank, fdtype, form, longer);
+        if (words == 3 && kind == kPacked) return pick_form<N, 3, kPacked>(rank, fdtype, form, steps);
+        if (words == 8 && kind == kWord32) return pick_form<N, 8, kWord32>(rank, fdtype, form, steps);
     } else {
-        if (words == 3 && kind == kPacked) return pick_form<N, 3, kPacked>(rank, fdtype, form, longer);
-        if (words == 8 && kind == kHalf16) return pick_form<N, 8, kHalf16>(rank, fdtype, form, longer);
-        if (words == 12 && kind == kWord32) return pick_form<N, 12, kWord32>(rank, fdtype, form, longer);
+        if (words == 3 && kind == kPacked) return pick_form<N, 3, kPacked>(rank, fdtype, form, steps);
+        if (words == 8 && kind == kHalf16) return pick_form<N, 8, kHalf16>(rank, fdtype, form, steps);
+        if (words == 12 && kind == kWord32) return pick_form<N, 12, kWord32>(rank, fdtype, form, steps);
     }
     return nullptr;
 }

@@ -4,8 +4,8 @@
 
 namespace spt {
 
-EcFnPtr pick_ec_n2(int rank, int fdtype, int words, int kind, EcForm form, bool longer) {
-    return pick_layout<2>(rank, fdtype, words, kind, form, longer);
+EcFnPtr pick_ec_n2(int rank, int fdtype, int words, int kind, EcForm form, int steps) {
+    return pick_layout<2>(rank, fdtype, words, kind, form, steps);
 }
 
 }  // namespace spt

@@ -64,26 +64,30 @@ enum class EcForm { kPlain, kReuse, kOrdered };
 constexpr int kEcMaxWaves = 8;
 // Split rows of a partition the elementwise kernel keeps in LDS.
 constexpr int kEcMaxSplit = 64;
-// Records a lane stages per step of the elementwise kernel.  The L lanes of a
-// nonzero (rank / 4, or rank / 8 with BF16 factors) stage L records at a time;
-// with L = 4 a step is then one batch of gathers and every step waits for its
+// Lanes of a nonzero: each loads 16 bytes of a factor row.
+constexpr int ec_lanes(int rank, bool bf16) { return rank / (bf16 ? 8 : 4); }
+// Records a lane stages per step of the elementwise kernel, for partitions of
+// `per` nonzeros.  The L lanes of a nonzero stage L records at a time; with
+// L = 4 a step is then one batch of gathers and every step waits for its
 // records, its staging and its gathers in turn.  Two records per lane make it
 // two batches, which overlap (4-mode 1e7, R 16: 117-138 -> 112-133 us); four
-// pay where a partition is long (`longer`; 4-mode 5e7, R 16: 739-903 -> 629-782
-// us; 1e7: 127-139).  With fewer or more lanes more records cost registers and
-// LDS, so occupancy, for nothing (5-mode 2e7, R 8: 206-239 -> 229-276 us; 5-mode
-// 5e7, R 32: 720-797 -> 864-1024, the reuse form lost).
-constexpr int ec_step_records(int rank, bool bf16, bool longer) {
-    return rank / (bf16 ? 8 : 4) == 4 ? (longer ? 4 : 2) : 1;
+// pay where a partition is long (4-mode 5e7, R 16: 739-903 -> 629-782 us; 1e7:
+// 127-139); where it is short the second batch finds no records (5-mode, R 16,
+// 4096 partitions of 36: 74 -> 58 us with one, of 146: 117 -> 106; 32768 of 586:
+// 1980 -> 2085).  With fewer or more lanes more records cost registers and LDS,
+// so occupancy, for nothing (5-mode 2e7, R 8: 206-239 -> 229-276 us; 5-mode 5e7,
+// R 32: 720-797 -> 864-1024, the reuse form lost).
+constexpr int ec_step_records(int rank, bool bf16, int64_t per) {
+    return ec_lanes(rank, bf16) == 4 ? (per >= 4096 ? 4 : per >= 256 ? 2 : 1) : 1;
 }
-// Dynamic LDS of an elementwise workgroup of `waves` waves: the lane groups'
-// head and tail partials, each wave's staged records (indices, value, carry
-// slot), per group its tail partial's row and slot, flags and the rows on
-// either side; each wave's copy of the partition's split rows and slots.
-constexpr int ec_lds_bytes(int nmodes, int rank, int fdtype, int waves, bool longer) {
-    const int per_load = fdtype == 0 ? 4 : 8;  // factor values a lane loads at once
-    const int groups = 64 * per_load / rank;
-    return waves * (2 * groups * rank * 4 + (nmodes + 2) * 64 * 4 * ec_step_records(rank, fdtype != 0, longer) + groups * 5 * 4 + 2 * kEcMaxSplit * 4);
+// Dynamic LDS of an elementwise workgroup of `waves` waves whose lanes stage
+// `steps` records: the lane groups' head and tail partials, each wave's staged
+// records (indices, value, carry slot), per group its tail partial's row and
+// slot, flags and the rows on either side; each wave's copy of the partition's
+// split rows and slots.
+constexpr int ec_lds_bytes(int nmodes, int rank, int fdtype, int waves, int steps) {
+    const int groups = 64 / ec_lanes(rank, fdtype != 0);
+    return waves * (2 * groups * rank * 4 + (nmodes + 2) * 64 * 4 * steps + groups * 5 * 4 + 2 * kEcMaxSplit * 4);
 }
 
 // fdtype 0: FP32 factors, 1: BF16 factors.  Returns false if the combination
