@@ -141,16 +141,18 @@ struct EcChoice {
 
 // Where the lines lie (MI355X, us per launch, plain / reuse form unless said):
 // - The reuse form saves a share `repeats` of one of the N-1 gathers and pays
-//   with a branch per nonzero.  With N >= 4 that pays at every
+//   with a branch per nonzero.  With N >= 4 that pays or costs nothing at every
 //   share measured (4-mode 1e7, R 16, repeats 0.15-0.71: 136-152 / 122-145;
 //   4-mode 1e8, R 64: 2692-2861 / 2282-2487; 5-mode 5e7, R 32: 860-901 /
-//   721-802).  With N = 3 it
+//   721-802; repeats 0.00-0.06: within 1 %), once partitions hold a few hundred
+//   nonzeros (8-mode, R 64, 32768 of 8: 570 / 800).  With N = 3 it
 //   pays on large skewed tensors (8e7, R 32: 982-1007 / 905-955; 2e7, repeats
 //   0.23-0.66: 240-246 / 226-233), not where most rows differ (8e7, repeats
 //   0.04-0.20: 1532-2053 / 1564-2106) and not on small tensors, whose rows
 //   hit the caches anyway (5e6, R 32, repeats 0.51-0.57: 57-61 / 60-66; 3e5,
 //   R 64, 147 partitions: 20-24 / 22-26), unless the rows are long (4e6, R 128,
-//   repeats 0.52-0.55: 149-157 / 137-141; 4e6, R 64: 79-80 / 74-75).  With N = 2 the kept row is the
+//   repeats 0.52-0.55: 149-157 / 137-141; 4e6, R 64: 79-80 / 74-75), nor in one
+//   wave per partition (1024 partitions of 73, R 128: 67 / 70).  With N = 2 the kept row is the
 //   only one, and every nonzero waits for the branch (1e7, R 32, repeats 0.45:
 //   89 / 113; R 64: 147 / 235; 3e7, R 64: 376 / 575).
 // - Waves per partition: up to 256 partitions leave CUs idle or with one
@@ -162,6 +164,19 @@ struct EcChoice {
 //   35 / 23 / 31).  Without rows to share (the plain form) and with enough
 //   partitions to fill the chip twice, 1 (8e7, zipf 0.8: 1981-2053 at 1,
 //   2042-2120 at 4).
+// - More waves pay only while each lane group still has records to walk: with few
+//   they cost their start and the combine.  Ratio of 4 waves to 1, all modes:
+//   64 partitions, R 16, of 73 nonzeros 1.0, of 146 0.85, R 64, of 36 0.95, of 73
+//   0.77 (8 to 4, R 16, of 293 0.98, of 586 0.93; BF16 at R 8, 64 groups a wave,
+//   4-mode 3e5, skewed: 8 waves 1.5); 300 partitions, R 32, of 73 0.89, R 16, of
+//   146 0.9 to 1.08 (8 modes); 1024 partitions, R 64, of 146 0.8, R 16, of 293 0.92
+//   (4 modes), 1.21 (5), of 586 0.91, 1.12; 2048, R 16, skewed, of 700 1.2, of 1030
+//   1.1, R 32, of 700 0.9, R 8, of 2047 1.1 to 1.3 (2 to 4 modes), 0.95 (5), 0.74
+//   (8), BF16 at R 8, of 2047 1.2 to 1.5.  Beyond 2048 the chip is
+//   full with one wave each, and what counts is the rows a group gathers: 4096
+//   partitions, R 64, of 700 1.12 (2 and 3 modes), 0.94 (4), 0.87 (8); R 32, of
+//   1030 1.17 (3), 1.03 (4), 0.9 (8); R 16, of 1030 1.15 to 1.0; at the default's
+//   2048 per partition 0.7 to 0.95 throughout.
 // - CP-ALS feeds its results back, so a change of rounding grows from sweep to
 //   sweep: its sums stay those of one wave per partition, bit for bit.  There
 //   the reuse form pays only where the partitions fill the chip (4-mode 1e8:
@@ -171,6 +186,21 @@ struct EcChoice {
 //   26-38; 3-mode 3.5e6, R 32, 1710: 50-52 / 47-48; 5e6, 2442: 69-85 / 85-90;
 //   eight waves up to 256 partitions, 3e5, R 64, 147: 76 / 63; 1e5, R 16, 49:
 //   31 / 26; two above: four gain nothing more at 977 and lose at 1710, 74).
+
+// Waves per partition for kappa partitions of `per` nonzeros, of which one wave's
+// G lane groups take per / G each.
+int ec_waves(int nmodes, int kappa, int64_t per, int G) {
+    if (kappa <= 256) {
+        if (G <= 32 && per >= std::min(1024, std::max(256, 32 * G))) return 8;
+        return per >= std::min(1024, std::max(32, 8 * G)) ? 4 : 1;
+    }
+    if (kappa <= 512) return per >= std::min(1024, 10 * G) ? 4 : 1;
+    if (kappa <= 1024) return per >= std::min(1024, 40 * G) ? 4 : 1;
+    if (kappa <= 2048) return per >= (nmodes >= 5 ? 63 : 70) * G ? 4 : 1;
+    if (per >= 2000) return 4;
+    const double rows = (double)per * (nmodes - 1);
+    return per >= 75 * G && rows * rows >= 1250.0 * 1250.0 * G ? 4 : 1;
+}
 
 EcChoice choose_ec(int nmodes, int rank, int fdtype, int words, int kind, int kappa, const EcArgs& a) {
 #ifdef SPT_EC_ONE_WAVE  // build option: the order of one wave for every caller
@@ -191,7 +221,7 @@ EcChoice choose_ec(int nmodes, int rank, int fdtype, int words, int kind, int ka
     const int steps = ec_step_records(rank, fdtype != 0, per);
     EcChoice c{pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kPlain, steps), 1, steps};
     if (!c.f) return c;
-    if (!one_wave) c.waves = kappa <= 256 ? 8 : 4;
+    if (!one_wave) c.waves = ec_waves(nmodes, kappa, per, 64 / lanes);
 #ifdef SPT_EC_FORM  // build option: 0 = always the plain form, 1 = always the reuse form
     const bool want = SPT_EC_FORM != 0;
 #else
@@ -200,9 +230,9 @@ EcChoice choose_ec(int nmodes, int rank, int fdtype, int words, int kind, int ka
     if (lanes == 4 && steps == 1)
         want = false;  // (that step has no reuse form)
     else if (nmodes >= 4)
-        want = !one_wave || kappa >= 4096;
+        want = one_wave ? kappa >= 4096 : per >= 256;
     else if (nmodes == 3 && a.repeats >= 0.4f)
-        want = kappa >= 4096 || (long_rows && !one_wave);
+        want = one_wave ? kappa >= 4096 : c.waves > 1 && (kappa >= 4096 || long_rows);
     if (want) {
         const EcFnPtr reuse = pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kReuse, steps);
         want = reuse && reuse_fits(c.f, reuse, ec_lds_bytes(nmodes, rank, fdtype, 1, steps));
