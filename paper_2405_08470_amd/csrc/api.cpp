@@ -283,6 +283,7 @@ spt_status launch_mode(spt_tensor_s* t, int mode, const uint32_t* rec_in, uint32
     a.one_wave = als ? 1 : 0;
     for (int k = 0; k < N; ++k) {
         const int w = (mode + k) % N;
+        if (k > 0) a.gathered += t->dims[w] * rank * (fdtype == SPT_BF16 ? 2 : 4);
         a.fac[k] = factors[w];
         a.rot[k] = w;
         a.foff[k] = t->lay.off[k];

@@ -177,6 +177,11 @@ struct EcChoice {
 //   partitions, R 64, of 700 1.12 (2 and 3 modes), 0.94 (4), 0.87 (8); R 32, of
 //   1030 1.17 (3), 1.03 (4), 0.9 (8); R 16, of 1030 1.15 to 1.0; at the default's
 //   2048 per partition 0.7 to 0.95 throughout.
+// - Beyond 1024 partitions, where few nonzeros share rows and these do not fit an
+//   XCD's L2 (4 MB; 6 as some of it stays), lines from beyond L2 are the bound and
+//   more waves crowd them out (5-mode 1e7, R 64, repeats 0.06, 9 MB: 3600 at 1,
+//   3920 at 4; 4-mode 3e7, R 32, 0.03, 10 MB: 3780 / 3970; 2-mode 3e6, R 8, 0.00,
+//   8 MB: 104 / 134; against 5-mode 1e7, R 32, 5 MB: 1405 / 1335).
 // - CP-ALS feeds its results back, so a change of rounding grows from sweep to
 //   sweep: its sums stay those of one wave per partition, bit for bit.  There
 //   the reuse form pays only where the partitions fill the chip (4-mode 1e8:
@@ -189,13 +194,14 @@ struct EcChoice {
 
 // Waves per partition for kappa partitions of `per` nonzeros, of which one wave's
 // G lane groups take per / G each.
-int ec_waves(int nmodes, int kappa, int64_t per, int G) {
+int ec_waves(int nmodes, int kappa, int64_t per, int G, bool crowded) {
     if (kappa <= 256) {
         if (G <= 32 && per >= std::min(1024, std::max(256, 32 * G))) return 8;
         return per >= std::min(1024, std::max(32, 8 * G)) ? 4 : 1;
     }
     if (kappa <= 512) return per >= std::min(1024, 10 * G) ? 4 : 1;
     if (kappa <= 1024) return per >= std::min(1024, 40 * G) ? 4 : 1;
+    if (crowded) return 1;
     if (kappa <= 2048) return per >= (nmodes >= 5 ? 63 : 70) * G ? 4 : 1;
     if (per >= 2000) return 4;
     const double rows = (double)per * (nmodes - 1);
@@ -218,10 +224,16 @@ EcChoice choose_ec(int nmodes, int rank, int fdtype, int words, int kind, int ka
             return {ordered, kappa <= 256 ? 8 : 2, 1};
     const int64_t per = a.nnz / kappa;
     const int lanes = ec_lanes(rank, fdtype != 0);
-    const int steps = ec_step_records(rank, fdtype != 0, per);
+    const bool crowded = a.repeats < 0.1f && a.gathered > (int64_t(6) << 20);
+    // a second record per lane costs more than it hides where lines from beyond L2
+    // are the bound and the chip is just full (2-mode 4e6, R 16: 79 us, 75 with one),
+    // and on skewed 3-mode tensors with BF16, whose staging is the larger (9e6, R 32:
+    // 112 in the reuse form, 92 with one in the plain form; 2e6: 38, 33)
+    const bool one = (crowded && kappa > 1024 && kappa <= 2048) || (nmodes == 3 && fdtype != 0 && a.repeats >= 0.1f);
+    const int most = ec_step_records(rank, fdtype != 0, per), steps = one && most == 2 ? 1 : most;
     EcChoice c{pick_ec(nmodes, rank, fdtype, words, kind, EcForm::kPlain, steps), 1, steps};
     if (!c.f) return c;
-    if (!one_wave) c.waves = ec_waves(nmodes, kappa, per, 64 / lanes);
+    if (!one_wave) c.waves = ec_waves(nmodes, kappa, per, 64 / lanes, crowded);
 #ifdef SPT_EC_FORM  // build option: 0 = always the plain form, 1 = always the reuse form
     const bool want = SPT_EC_FORM != 0;
 #else

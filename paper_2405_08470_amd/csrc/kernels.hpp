@@ -28,6 +28,7 @@ struct EcArgs {
     uint32_t fmask[8];         // width mask of each mode's index (packed layout)
     int64_t nnz;
     float repeats;             // ModePlan::repeats of mode d
+    int64_t gathered;          // bytes of the other modes' factors
     int32_t one_wave;          // 1: one wave per partition, whose order of summation CP-ALS keeps
     int32_t waves;             // waves per partition (set by launch_ec)
 };
