@@ -57,13 +57,10 @@ __device__ __forceinline__ uint32_t decode(const Rec<RW>& r, const EcArgs& a) {
 
 // Orders a wave's LDS accesses before and after it (the waves of a workgroup
 // keep their own staging, so no workgroup barrier is needed).  LDS accesses of
-// one wave are carried out in order, so this only holds the compiler; the lane
-// exchange of a constant makes every lane of the wave take part and costs
-// nothing.
+// one wave are carried out in order, so this only holds the compiler.
 __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    (void)__builtin_amdgcn_readlane(0, 0);
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 

@@ -104,7 +104,7 @@ inline int __builtin_amdgcn_ds_bpermute(int addr, int v) { return cpuhip::bpermu
 inline int __builtin_amdgcn_readlane(int v, int lane) { return cpuhip::readlane(v, lane); }
 inline float __shfl_xor(float v, int mask, int width = 64) { return cpuhip::shfl_xor(v, mask, width); }
 inline void __builtin_amdgcn_fence(int, const char*) {}
-inline void __builtin_amdgcn_wave_barrier() {}
+inline void __builtin_amdgcn_wave_barrier() { (void)cpuhip::readlane(0, 0); }  // every lane of the wave must arrive
 
 template <typename F, typename... A>
 inline void hipLaunchKernelGGL(F kernel, dim3 grid, dim3 block, size_t shmem, hipStream_t, A... args) {
