@@ -102,7 +102,8 @@ typedef struct spt_info {
     int32_t nmodes;
     int32_t cur_mode;        /* mode whose order the stream is in            */
     int32_t kappa;
-    int32_t record_bytes;    /* bytes of one packed nonzero record (16/32)   */
+    int32_t record_bytes;    /* bytes of one packed nonzero record: 12, 16,
+                                32 or 48                                     */
     int64_t nnz;
     int64_t dims[8];
     int64_t max_load[8];     /* largest partition of each mode (nonzeros)    */
@@ -186,10 +187,10 @@ spt_status spt_mttkrp(spt_tensor_t t, int32_t mode, const void *const *factors,
  *   fit      host double*, receives 1 - ||X - Xhat|| / ||X|| (synchronises
  *            the stream); NULL to skip
  * The stream must be in mode 0's order on entry and is on exit.  With
- * opts.dr = 0 each mode's remap pass runs on a side stream the handle owns
- * (default priority), beside that mode's fixup and factor update; the
- * caller's stream waits for it before the next mode, so all of the call's
- * work is ordered on `stream` as usual.
+ * opts.dr = 0 and 2^21 or more nonzeros each mode's remap pass runs on a side
+ * stream the handle owns (default priority), beside that mode's fixup and
+ * factor update; the caller's stream waits for it before the next mode, so all
+ * of the call's work is ordered on `stream` as usual.
  * Device workspace is allocated on first use per rank and kept by the
  * handle.  Errors: STATE, UNSUPPORTED, NOT_SPD (reported by the call that
  * synchronises: this one when fit != NULL, else the next), HIP, OOM.
@@ -211,8 +212,10 @@ spt_status spt_cp_als_iter(spt_tensor_t t, void *const *factors, spt_dtype fdtyp
  *   grads    host array of nmodes device float pointers, overwritten
  *   loss     device double[1], overwritten
  * rank 8, 16, 32 or 64; FP32 factors.  The tensor's stream must be in mode
- * 0's order (it is read, not moved).  The residual streams are allocated on
- * first use and kept by the handle.  Errors: STATE, UNSUPPORTED, HIP, OOM.
+ * 0's order (it is read, not moved).  Three residual streams (two modes or one
+ * copy per mode: two) of one record per nonzero are allocated on first use and
+ * kept by the handle; the last is done without, for one more pass, if it cannot
+ * be had.  Errors: STATE, UNSUPPORTED, HIP, OOM.
  */
 spt_status spt_cp_gradient(spt_tensor_t t, const void *const *factors, spt_dtype fdtype,
                            int32_t rank, void *const *grads, double *loss, void *stream);
@@ -229,10 +232,8 @@ spt_status spt_cp_gradient(spt_tensor_t t, const void *const *factors, spt_dtype
  * need returns SPT_ERR_UNSUPPORTED with the size in spt_last_error().  The
  * buffer needs no clearing: every slot a call reads was written earlier in
  * that call.  All calls on one device share it, so calls that overlap on one
- * device (other streams, other threads) race; serialise them.  Hot-row
- * tables are used when an earlier spt_mttkrp call built them for this rank
- * and factor type, else every factor row is read from memory (same results).
- * No kernel timing is recorded.
+ * device (other streams, other threads) race; serialise them.  No kernel
+ * timing is recorded.
  */
 spt_status spt_mttkrp_noalloc(spt_tensor_t t, int32_t mode, const void *const *factors,
                               spt_dtype fdtype, int32_t rank, float *out, uint32_t flags,
@@ -252,7 +253,9 @@ spt_status spt_cp_loss(spt_tensor_t t, const void *const *factors, spt_dtype fdt
  * MTTKRP of the residual stream of the last spt_cp_loss (or
  * spt_cp_gradient) call on this handle, for every mode d (Eq. (1) with the
  * residuals as values).  `factors` must be the ones that call was given.  The
- * residual stream is left in mode 0's order, so the call may be repeated.
+ * residual stream is left in mode 0's order, so the call may be repeated, and a
+ * captured one replayed (but for three, five or seven modes without the third
+ * stream).
  * Errors: STATE (no residual stream of this rank yet), UNSUPPORTED, HIP, OOM.
  */
 spt_status spt_cp_adjoint(spt_tensor_t t, const void *const *factors, spt_dtype fdtype,

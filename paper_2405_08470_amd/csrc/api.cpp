@@ -101,8 +101,9 @@ struct spt_tensor_s {
     };
     SweepResult* result = nullptr;  // pinned host memory
     hipEvent_t status_event = nullptr;
-    // CP-ALS: the remap pass of a mode on a side stream, beside that mode's
-    // fixup and dense update (joined before the next mode's EC)
+    // CP-ALS from kSideRemapFrom nonzeros: the remap pass of a mode on a side
+    // stream, beside that mode's fixup and dense update (joined before the next
+    // mode's EC)
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     bool join_pending = false;
@@ -226,10 +227,7 @@ hipEvent_t mark(spt_tensor_s* t, hipStream_t s) {
 
 // Nonzeros from which CP-ALS runs the remap pass on the side stream.  The fork
 // and join between the streams cost about 10 us per mode.
-#ifndef SPT_SIDE_FROM
-#define SPT_SIDE_FROM (2 << 20)
-#endif
-constexpr int64_t kSideRemapFrom = SPT_SIDE_FROM;
+constexpr int64_t kSideRemapFrom = 2 << 20;
 
 spt_status ensure_side(spt_tensor_s* t) {
     if (t->side) return SPT_OK;
@@ -248,8 +246,9 @@ spt_status join_side(spt_tensor_s* t, hipStream_t s) {
 }
 
 // EC (+ remap into rec_out when it is not null) and fixup for one mode over
-// the stream rec_in, which must be in that mode's order.  With side_remap the
-// remap pass runs on the tensor's side stream after EC, and the caller must
+// the stream rec_in, which must be in that mode's order.  `als`: the sums are
+// added in the order of one wave per partition, and from kSideRemapFrom nonzeros
+// the remap pass runs on the tensor's side stream after EC; the caller must then
 // call join_side() before anything on s reads rec_out.
 // With noalloc_carry != nullptr the call allocates nothing: the split-row
 // partial sums go to that buffer and no timing events are recorded.
@@ -871,7 +870,8 @@ spt_status spt_cp_als_iter(spt_tensor_t t, void* const* factors, spt_dtype fdtyp
         if (bf16) spt::launch_to_bf16((const float*)factors[w], t->shadow[w], t->dims[w] * rank, s);
     }
     for (int d = 0; d < N; ++d) {
-        // the remap pass of mode d overlaps its fixup and dense update
+        // from kSideRemapFrom nonzeros the remap pass of mode d overlaps its fixup
+        // and dense update
         st = run_mttkrp(t, d, gath, fdtype, rank, t->M, true, s, true);
         if (st != SPT_OK) return st;
         spt::launch_normal_inverse(rank, N, d, t->grams, t->Vinv, t->status, s);

@@ -171,12 +171,12 @@ struct EcChoice {
 //   4-mode 3e5, skewed: 8 waves 1.5); 300 partitions, R 32, of 73 0.89, R 16, of
 //   146 0.9 to 1.08 (8 modes); 1024 partitions, R 64, of 146 0.8, R 16, of 293 0.92
 //   (4 modes), 1.21 (5), of 586 0.91, 1.12; 2048, R 16, skewed, of 700 1.2, of 1030
-//   1.1, R 32, of 700 0.9, R 8, of 2047 1.1 to 1.3 (2 to 4 modes), 0.95 (5), 0.74
+//   1.1, R 32, of 700 0.75 to 0.95, R 8, of 2047 1.1 to 1.3 (2 to 4 modes), 0.95 (5), 0.74
 //   (8), BF16 at R 8, of 2047 1.2 to 1.5.  Beyond 2048 the chip is
 //   full with one wave each, and what counts is the rows a group gathers: 4096
 //   partitions, R 64, of 700 1.12 (2 and 3 modes), 0.94 (4), 0.87 (8); R 32, of
-//   1030 1.17 (3), 1.03 (4), 0.9 (8); R 16, of 1030 1.15 to 1.0; at the default's
-//   2048 per partition 0.7 to 0.95 throughout.
+//   1030 1.17 (3), 1.03 (4), 0.9 (8); R 16, of 1030 1.2 to 1.0; at the default's
+//   2048 per partition 0.7 to 1.0.
 // - Beyond 1024 partitions, where few nonzeros share rows and these do not fit an
 //   XCD's L2 (4 MB; 6 as some of it stays), lines from beyond L2 are the bound and
 //   more waves crowd them out (5-mode 1e7, R 64, repeats 0.06, 9 MB: 3600 at 1,

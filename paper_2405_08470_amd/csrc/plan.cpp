@@ -278,8 +278,9 @@ void plan_mode(int d, const int64_t* dims, int64_t nnz, const int32_t* idx, int3
 int32_t default_kappa(int64_t nnz) {
     // about 2048 nonzeros per partition, at most 8192 partitions: fewer, larger
     // partitions give the remap longer runs of adjacent destinations, and 8192
-    // one-wave workgroups still fill the chip (measured over kappa 2048..65536
-    // on 50M..100M-nonzero tensors)
+    // workgroups of one wave still fill the chip (measured over kappa 2048..65536
+    // on 50M..100M-nonzero tensors with one wave per partition; not again with
+    // the several waves that the launch takes since)
     int64_t k = (nnz + 2047) / 2048;
     return (int32_t)std::min<int64_t>(8192, std::max<int64_t>(1, k));
 }
