@@ -394,6 +394,12 @@ struct Temps {
     }
 };
 
+// Nonzeros from which the remap ids are copied to the host beside other work
+// (load, ms, in the call's stream / beside: 4e5 nonzeros 5.2 / 6.5, 1e6 7.5 / 7.8,
+// 4e6 11.7 / 11.5, 1e7 30.9 / 24.2: the copies' page faults and staging; below, the
+// second stream and the thread).
+constexpr int64_t kCopyBesideFrom = 2 << 20;
+
 // A second stream for the length of a call.
 struct SideStream {
     hipStream_t stream = nullptr;
@@ -570,9 +576,10 @@ DevicePlanError build_plan_device(int N, const int64_t* dims, int64_t nnz, const
         if (!copies) {
             // host memory of mode 0's remap ids, its pages touched meanwhile
             out->remap0.reset(new int32_t[std::max<int64_t>(1, nnz)]);
-            lpt.th.emplace_back([p = out->remap0.get(), nnz] {
-                for (int64_t i = 0; i < nnz; i += 1024) p[i] = 0;
-            });
+            if (nnz >= kCopyBesideFrom)
+                lpt.th.emplace_back([p = out->remap0.get(), nnz] {
+                    for (int64_t i = 0; i < nnz; i += 1024) p[i] = 0;
+                });
         }
         for (int w = 0; w < N; ++w) {
             rowK[w] = tmp.alloc<uint32_t>(nnz);
@@ -627,6 +634,10 @@ DevicePlanError build_plan_device(int N, const int64_t* dims, int64_t nnz, const
             pa.bits[w] = lay.bits[w];
         }
         std::vector<int32_t*> remap(N);
+        // mode 0's remap ids come to the host (spt_tensor_get_remap reads them).  A
+        // copy to pageable memory holds the thread that asks for it, so where it is
+        // large another thread asks, beside the rest of the work
+        const bool beside = !copies && nnz >= kCopyBesideFrom;
         hipError_t copied = hipSuccess;
         JoinAll copier;  // (ends before what it reads and writes)
         for (int w = 0; w < N; ++w) remap[w] = tmp.alloc<int32_t>(nnz);
@@ -646,22 +657,17 @@ DevicePlanError build_plan_device(int N, const int64_t* dims, int64_t nnz, const
                        (const int32_t*)(didx + d * nnz), (const int32_t*)(didx + (d + N - 1) % N * nnz), nnz,
                        same + d * kRunWindows);
             if (nnz > 0) launch(scatter_pos_kernel, g, kT, s, (const int32_t*)sb.v[0], nnz, remap[d]);
-            if (d == 0 && !copies) {
-                // mode 0's remap ids come to the host (spt_tensor_get_remap reads
-                // them) beside the rest of the work: a copy to pageable memory
-                // holds the thread that asks for it, so another one does
-                if (nnz > 0) {
-                    side.fork(s);
-                    int dev = 0;
-                    check(hipGetDevice(&dev), "device");
-                    copier.th.emplace_back([&, dev] {
-                        copied = hipSetDevice(dev);
-                        if (copied == hipSuccess)
-                            copied = hipMemcpyAsync(out->remap0.get(), remap[0], sizeof(int32_t) * nnz,
-                                                    hipMemcpyDeviceToHost, side.stream);
-                        if (copied == hipSuccess) copied = hipStreamSynchronize(side.stream);
-                    });
-                }
+            if (d == 0 && beside) {
+                side.fork(s);
+                int dev = 0;
+                check(hipGetDevice(&dev), "device");
+                copier.th.emplace_back([&, dev] {
+                    copied = hipSetDevice(dev);
+                    if (copied == hipSuccess)
+                        copied = hipMemcpyAsync(out->remap0.get(), remap[0], sizeof(int32_t) * nnz,
+                                                hipMemcpyDeviceToHost, side.stream);
+                    if (copied == hipSuccess) copied = hipStreamSynchronize(side.stream);
+                });
             }
             if (copies || d == 0) {
                 uint32_t* r = static_cast<uint32_t*>(palloc(sizeof(uint32_t) * lay.words * nnz));
@@ -719,6 +725,9 @@ DevicePlanError build_plan_device(int N, const int64_t* dims, int64_t nnz, const
         if (nnz > 0)
             check(hipMemcpyAsync(hsame.data(), same, sizeof(int32_t) * hsame.size(), hipMemcpyDeviceToHost, s),
                   "download");
+        if (nnz > 0 && !copies && !beside)
+            check(hipMemcpyAsync(out->remap0.get(), remap[0], sizeof(int32_t) * nnz, hipMemcpyDeviceToHost, s),
+                  "download remap ids");
         check(hipStreamSynchronize(s), "device planner");
         copier.join();
         check(copied, "download remap ids");

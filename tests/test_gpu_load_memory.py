@@ -1,6 +1,7 @@
 """A handle of the device planner holds the device memory of the host planner's
 and gives the same remap ids: nothing of the load is left on the device for
-spt_tensor_get_remap.  Sizes: none, one and many nonzeros.
+spt_tensor_get_remap.  Sizes: none, one and many nonzeros, and both sides of the
+line from which the remap ids are copied beside the rest of the load (2^21).
 """
 import numpy as np
 import pytest
@@ -15,7 +16,7 @@ if not torch.cuda.is_available():  # pragma: no cover
 S = pytest.importorskip("paper_2405_08470_amd.spmttkrp")
 
 
-@pytest.mark.parametrize("nnz", [0, 1, 100_000])
+@pytest.mark.parametrize("nnz", [0, 1, 100_000, (1 << 21) - 1, 1 << 21])
 @pytest.mark.parametrize("kw", [{}, {"remap": "fused"}, {"copies": 1}], ids=["staged", "fused", "copies"])
 def test_device_planner_holds_no_more_than_the_host_planner(nnz, kw):
     print("case", nnz, kw, flush=True)
